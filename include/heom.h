@@ -215,7 +215,10 @@ heom_status heom_rhs(const heom_hierarchy* h, heom_state in, heom_state out, int
  * Synchronous: returns after the stream has finished; if host_out != NULL
  * the records are copied to host_out [n_rec][heom_record_doubles].
  * HEOM_E_UNSTABLE if dt exceeds the RK4 bound for the problem's rates;
- * HEOM_E_NUMERIC if a recorded observable was not finite.  Runs of 8 steps
+ * HEOM_E_NUMERIC if a recorded observable was not finite.  Small hierarchies
+ * (HEOM_FP64 and HEOM_FP32_MIXED, N <= 22, up to about 255 workgroups of 2048
+ * elements) run all their steps in one launch that keeps the state on the
+ * compute units.  Of the others, runs of 8 steps
  * or more launch the first step directly and replay a HIP graph of one step
  * (captured on a private stream) for the rest, unless kernel timing is on
  * (heom_timing_enable); the results are the same either way, bit for bit. */
@@ -314,7 +317,8 @@ heom_status heom_destroy(heom_hierarchy* h);
 
 /* Kernel timing, for benchmarks (process-wide, off by default).  While
  * enabled, heom_propagate brackets every launch of the bulk RK4 stage kernel
- * (ADOs u >= 1) with a pair of HIP events recorded on the caller's stream and,
+ * (ADOs u >= 1; for a small hierarchy the launches that take the whole run)
+ * with a pair of HIP events recorded on the caller's stream and,
  * after its final synchronisation, adds their elapsed times.  heom_timing_read
  * returns the accumulated milliseconds, the number of launches and the
  * algorithmic bytes those launches move (per RK4 step: 13 passes over the

@@ -2,19 +2,21 @@
 
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libheom.so")
-SOURCES = [os.path.join(CSRC, "heom_kernels.hip"), os.path.join(CSRC, "heom_host.cpp"),
-           os.path.join(CSRC, "heom_server.cpp"), os.path.join(CSRC, "heom_scratch.hip")]
+SOURCES = [os.path.join(CSRC, f) for f in ("heom_kernels.hip", "heom_resident.hip", "heom_host.cpp",
+                                           "heom_server.cpp", "heom_scratch.hip")]
 
 HIPCC_FLAGS = [
-    "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
+    "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
     # no packed-FP32 instructions in device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
@@ -29,11 +31,20 @@ def hipcc():
 
 
 def build(verbose=False):
-    cmd = [hipcc(), *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC, *SOURCES,
-           "-o", LIB + ".tmp"]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    """Compile every source (side by side) and link the library."""
+    with tempfile.TemporaryDirectory() as tmp:
+        cmds = []
+        for src in SOURCES:
+            obj = os.path.join(tmp, os.path.basename(src) + ".o")
+            cmds.append([hipcc(), *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                         "-c", src, "-o", obj])
+        if verbose:
+            for cmd in cmds:
+                print(" ".join(cmd), flush=True)
+        with concurrent.futures.ThreadPoolExecutor(max_workers=4) as pool:
+            list(pool.map(lambda cmd: subprocess.run(cmd, check=True), cmds))
+        subprocess.run([hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950",
+                        *[cmd[-1] for cmd in cmds], "-o", LIB + ".tmp"], check=True)
     os.replace(LIB + ".tmp", LIB)
     return LIB
 

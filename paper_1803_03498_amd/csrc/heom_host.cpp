@@ -11,6 +11,7 @@
 #include <atomic>
 #include <chrono>
 #include <cmath>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -799,6 +800,112 @@ struct StepGraph {
     }
 };
 
+// Resident grid launches spin at their barriers, so all of a launch's
+// workgroups have to fit the GPU at once.  Two launches do (see
+// heom_resident.hip): at most two run at a time on a device, further ones
+// wait here for their turn.  The caller's stream is idle when the permit is
+// taken, so nothing is waited for while it is held but the launch itself.
+class ResidentPermit {
+public:
+    explicit ResidentPermit(bool needed) {
+        if (!needed) return;
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        slot_ = &slots_[dev & 63];
+        std::unique_lock<std::mutex> lk(slot_->mu);
+        slot_->cv.wait(lk, [&] { return slot_->running < 2; });
+        ++slot_->running;
+    }
+    ~ResidentPermit() {
+        if (!slot_) return;
+        std::lock_guard<std::mutex> lk(slot_->mu);
+        --slot_->running;
+        slot_->cv.notify_one();
+    }
+    ResidentPermit(const ResidentPermit&) = delete;
+    ResidentPermit& operator=(const ResidentPermit&) = delete;
+
+private:
+    struct Slot {
+        std::mutex mu;
+        std::condition_variable cv;
+        int running = 0;
+    };
+    static Slot slots_[64];
+    Slot* slot_ = nullptr;
+};
+ResidentPermit::Slot ResidentPermit::slots_[64];
+
+// Steps per resident launch (bounds the time one launch holds its compute
+// units: about 50 ms at 3060 ADOs), and the bound of each of its waits (0.2 s).
+constexpr int64_t kResidentSteps = 4096;
+constexpr uint64_t kResidentWaitTicks = 20000000ull;
+// this thread's bound instead, for tests of a launch that gives up
+thread_local int64_t t_resident_wait_ticks = -1;
+using heom::kResidentFlagBytes;
+
+// The run by resident launches.  Workspace: control block (commit word at
+// 512) | flags | two sigma_0 copies | two stage copies.  *done: committed
+// steps; fewer than n_steps if a launch gave up.
+heom_status resident_run(const heom_hierarchy* h, const heom::Job& j, const heom::ResidentPlan& plan,
+                         char* w, const char* ctl, size_t ctl_bytes, int64_t n_steps, bool timed,
+                         double* host_out, int64_t out_doubles, hipStream_t st, int64_t* done,
+                         int32_t* status) {
+    heom::ResidentArgs a{};
+    char* at = w + ctl_bytes;
+    if (plan.grid) {
+        a.flags = reinterpret_cast<uint32_t*>(at);
+        at += kResidentFlagBytes;
+        for (int k = 0; k < 2; ++k) {
+            a.s0x[k] = at;
+            at += align256(h->info.sigma0_bytes);
+        }
+        for (int k = 0; k < 2; ++k) {
+            a.exch[k] = at;
+            at += align256(h->info.rest_bytes);
+        }
+    }
+    a.commit = reinterpret_cast<uint32_t*>(w + 512);
+    a.wait_ticks = t_resident_wait_ticks >= 0 ? (uint64_t)t_resident_wait_ticks : kResidentWaitTicks;
+    HIP_TRY(hipMemcpyAsync(w, ctl, ctl_bytes + (plan.grid ? kResidentFlagBytes : 0),
+                           hipMemcpyHostToDevice, st));
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    if (timed)
+        for (auto& e : ev) HIP_TRY(hipEventCreate(&e));
+    if (timed) HIP_TRY(hipEventRecord(ev[0], st));
+    int64_t launches = 0;
+    for (int64_t step = 0; step < n_steps; step += a.n_steps, ++launches) {
+        a.step0 = step;
+        a.n_steps = std::min(kResidentSteps, n_steps - step);
+        a.chunk = (uint32_t)launches;
+        a.epoch0 = (uint32_t)(4 * step);
+        if (plan.grid) HIP_TRY(hipStreamSynchronize(st));
+        ResidentPermit permit(plan.grid);
+        hipError_t e = heom::launch_resident(j, a, plan, h->d.precision, st);
+        if (e != hipSuccess) return fail(HEOM_E_DEVICE, "resident launch: %s", hipGetErrorString(e));
+        if (plan.grid) HIP_TRY(hipStreamSynchronize(st));
+    }
+    if (timed) HIP_TRY(hipEventRecord(ev[1], st));
+    alignas(8) char back[768];
+    HIP_TRY(hipMemcpyAsync(back, w, sizeof back, hipMemcpyDeviceToHost, st));
+    if (host_out)
+        HIP_TRY(hipMemcpyAsync(host_out, j.records, (size_t)out_doubles * 8, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    std::memcpy(done, back, 8);
+    std::memcpy(status, back + 256, 4);
+    if (timed) {
+        float ms = 0.0f;
+        HIP_TRY(hipEventElapsedTime(&ms, ev[0], ev[1]));
+        for (auto& e : ev) (void)hipEventDestroy(e);
+        std::lock_guard<std::mutex> lk(g_timing.mu);
+        g_timing.ms += ms;
+        g_timing.launches += launches;
+        g_timing.bytes += 13.0 * (double)h->info.rest_bytes * (double)*done;
+    }
+    if (*done == n_steps && *status) return fail(HEOM_E_NUMERIC, "non-finite observable");
+    return HEOM_OK;
+}
+
 // heom_propagate on a given workspace.  `timing` allows the benchmark event
 // timing (which creates HIP events) and `graphs` the step graph (which
 // allocates); the no-alloc entry point passes false for both.
@@ -834,16 +941,32 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
                                        kind == HEOM_OBS_DIPOLE ? obs->ground : 0, hermitian);
 
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // control block: step = 0, status = 0, mu (N <= 64: at most 1536 bytes)
-    alignas(16) char ctl[1024 + 64 * 8] = {};
-    const size_t ctl_bytes = std::min(heom::control_bytes(N), sizeof(ctl));
+    // control block: step = 0, status = 0, commit word = 0, mu (N <= 64: at
+    // most 1536 bytes), and behind it the flags of a resident launch
+    alignas(16) char ctl[1024 + 64 * 8 + kResidentFlagBytes] = {};
+    const size_t ctl_bytes = heom::control_bytes(N);
     if (kind == HEOM_OBS_DIPOLE) std::memcpy(ctl + 1024, obs->mu, N * 8);
+
+    const int tiles = h->t.n_ado > 1 ? j.n_tiles : 0;
+    const bool timed = timing && g_timing.enabled.load() && tiles > 0;
+    heom::ResidentPlan plan;
+    int64_t done = 0;
+    int32_t status = 0;
+    if (n_steps > 0 && h->d.precision != HEOM_FP32_HERM &&
+        heom::resident_plan(j, h->d.precision == HEOM_FP64 ? 8 : 4, &plan)) {
+        s = resident_run(h, j, plan, w, ctl, ctl_bytes, n_steps, timed, host_out, n_rec * rd, st, &done,
+                         &status);
+        if (s != HEOM_OK || done == n_steps) return s;
+        // given up (the GPU could not hold the launch): the stage kernels go
+        // on from the last committed step
+    }
+    std::memcpy(ctl, &done, 8);
+    std::memcpy(ctl + 256, &status, 4);
     HIP_TRY(hipMemcpyAsync(w, ctl, ctl_bytes, hipMemcpyHostToDevice, st));
 
     heom::StageSpec sp[4];
     heom::rk4_stage_specs(sp);
 
-    const int tiles = h->t.n_ado > 1 ? j.n_tiles : 0;
     if (h->d.precision == HEOM_FP32_HERM && j.n_low > 0 && tiles > 0) {
         // complex copies of the lower levels, alternating between the two
         // buffers: stage k reads the copy the previous stage wrote
@@ -854,7 +977,6 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
             sp[k].mirror_out = 2 - (k & 1);
         }
     }
-    const bool timed = timing && g_timing.enabled.load() && tiles > 0;
     std::vector<hipEvent_t> ev;
     if (timed) {
         ev.resize(2 * (size_t)n_steps * 4);
@@ -877,14 +999,14 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     // the device, so every replay is the same launch.  A capture that fails
     // falls back to direct launches.
     StepGraph graph(st);
-    int64_t step = 0;
-    if (graphs && !timed && tiles > 0 && n_steps >= kGraphMinSteps) {
-        hipError_t e = launch_step(0, st);
+    int64_t step = done;
+    if (graphs && !timed && tiles > 0 && n_steps - done >= kGraphMinSteps) {
+        hipError_t e = launch_step(step, st);
         if (e != hipSuccess)
             return fail(HEOM_E_DEVICE, "stage launch (%s): %s", heom::last_launch_failure(),
                         hipGetErrorString(e));
-        step = 1;
-        if (graph.capture([&](hipStream_t cs) { return launch_step(1, cs); })) {
+        ++step;
+        if (graph.capture([&](hipStream_t cs) { return launch_step(step, cs); })) {
             for (; step < n_steps; ++step)
                 if ((e = hipGraphLaunch(graph.exec, st)) != hipSuccess)
                     return fail(HEOM_E_DEVICE, "graph launch: %s", hipGetErrorString(e));
@@ -901,7 +1023,6 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
         hipError_t e = heom::launch_stage(j, nullptr, 0, 0, h->d.precision, sp[0], st);
         if (e != hipSuccess) return fail(HEOM_E_DEVICE, "record launch: %s", hipGetErrorString(e));
     }
-    int32_t status = 0;
     HIP_TRY(hipMemcpyAsync(&status, j.status, 4, hipMemcpyDeviceToHost, st));
     if (host_out)
         HIP_TRY(hipMemcpyAsync(host_out, j.records, (size_t)n_rec * rd * 8, hipMemcpyDeviceToHost, st));
@@ -909,7 +1030,7 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     if (timed) {
         double ms_total = 0.0, bytes = 0.0;
         const double pass = (double)h->info.rest_bytes;
-        for (int64_t step = 0; step < n_steps; ++step)
+        for (int64_t step = done; step < n_steps; ++step)
             for (int k = 0; k < 4; ++k) {
                 float ms = 0.0f;
                 HIP_TRY(hipEventElapsedTime(&ms, ev[2 * (step * 4 + k)], ev[2 * (step * 4 + k) + 1]));
@@ -919,7 +1040,7 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
         for (auto& x : ev) (void)hipEventDestroy(x);
         std::lock_guard<std::mutex> lk(g_timing.mu);
         g_timing.ms += ms_total;
-        g_timing.launches += 4 * n_steps;
+        g_timing.launches += 4 * (n_steps - done);
         g_timing.bytes += bytes;
     }
     if (status) return fail(HEOM_E_NUMERIC, "non-finite observable");
@@ -937,6 +1058,10 @@ heom_status heom_propagate(const heom_hierarchy* h, heom_state io, void* work_de
     return propagate_impl(h, io, work_dev, work_bytes, dt_fs, n_steps, record_every, obs,
                           hermitian, host_out, stream, true, true);
 }
+
+// Not part of the ABI: bounds the waits of this thread's resident launches
+// (100 MHz ticks; 0 = the first unanswered poll gives up, < 0 = the default).
+void heom_test_resident_wait(int64_t ticks) { t_resident_wait_ticks = ticks; }
 
 heom_status heom_propagate_noalloc(const heom_hierarchy* h, heom_state io, double dt_fs,
                                    int64_t n_steps, int32_t record_every,

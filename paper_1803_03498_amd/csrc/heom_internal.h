@@ -100,6 +100,36 @@ struct StageSpec {
     int32_t mirror_in, mirror_out;
 };
 
+// Resident propagation (heom_resident.hip): every step of a small hierarchy's
+// run in one launch.
+struct ResidentPlan {
+    bool grid;                    // a grid of workgroups, else one workgroup
+    int groups;                   // bulk workgroups (sigma_0's own group comes on top)
+    int slots, low_slots;         // ADOs per workgroup, and those that may lie below the top level
+    int ept, threads;             // elements per bulk thread, threads per workgroup
+    int bulk_threads;             // of those (one workgroup: the rest hold sigma_0)
+    size_t lds;
+};
+constexpr uint32_t kResidentAborted = 0xFFFFFFFFu;
+// flags 64 bytes apart: packed into 8 lines, the stores of one queue behind
+// the polls of the others (6.6 against 4.2 us per exchange of 256 workgroups)
+constexpr int kResidentFlagStride = 16;
+constexpr size_t kResidentFlagBytes = 256 * kResidentFlagStride * 4;
+struct ResidentArgs {
+    int32_t groups, slots, low_slots, bulk_threads;  // from the plan
+    int64_t n_steps, step0;       // steps of this launch, and those done before it
+    void* exch[2];                // stage outputs in turn: [n_ado-1][N][N]
+    void* s0x[2];                 // the same for sigma_0: complex128 [N][N]
+    uint32_t* flags;              // [256] at kResidentFlagStride, below epoch0 + 1 before the launch
+    uint32_t epoch0;              // stages of the launches before
+    uint32_t* commit;             // `chunk` before the launch; chunk + 1 = done, or kResidentAborted
+    uint32_t chunk;
+    uint64_t wait_ticks;          // bound of each wait, ticks of the 100 MHz clock
+};
+bool resident_plan(const Job& j, int tsize, ResidentPlan* plan);
+hipError_t launch_resident(const Job& j, const ResidentArgs& args, const ResidentPlan& plan,
+                           int precision, hipStream_t stream);
+
 // Launch-shape caps (heom_set_launch_shape; 0 = none).
 extern std::atomic<int> g_max_workgroups, g_max_ados_per_tile;
 
