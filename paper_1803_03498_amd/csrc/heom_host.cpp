@@ -844,6 +844,26 @@ constexpr uint64_t kResidentWaitTicks = 20000000ull;
 thread_local int64_t t_resident_wait_ticks = -1;
 using heom::kResidentFlagBytes;
 
+// n_steps by launches of at most kResidentSteps, each a call of launch()
+// with `a` set; the grid form's one by one under a permit.
+template <class F>
+hipError_t resident_launches(heom::ResidentArgs& a, bool grid, int64_t n_steps, hipStream_t st,
+                             int64_t* launches, F&& launch) {
+    hipError_t e = hipSuccess;
+    a.wait_ticks = t_resident_wait_ticks >= 0 ? (uint64_t)t_resident_wait_ticks : kResidentWaitTicks;
+    for (int64_t step = 0; step < n_steps; step += a.n_steps, ++*launches) {
+        a.step0 = step;
+        a.n_steps = std::min(kResidentSteps, n_steps - step);
+        a.chunk = (uint32_t)*launches;
+        a.epoch0 = (uint32_t)(4 * step);
+        if (grid && (e = hipStreamSynchronize(st)) != hipSuccess) return e;
+        ResidentPermit permit(grid);
+        if ((e = launch()) != hipSuccess) return e;
+        if (grid && (e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // The run by resident launches.  Workspace: control block (commit word at
 // 512) | flags | two sigma_0 copies | two stage copies.  *done: committed
 // steps; fewer than n_steps if a launch gave up.
@@ -866,7 +886,6 @@ heom_status resident_run(const heom_hierarchy* h, const heom::Job& j, const heom
         }
     }
     a.commit = reinterpret_cast<uint32_t*>(w + 512);
-    a.wait_ticks = t_resident_wait_ticks >= 0 ? (uint64_t)t_resident_wait_ticks : kResidentWaitTicks;
     HIP_TRY(hipMemcpyAsync(w, ctl, ctl_bytes + (plan.grid ? kResidentFlagBytes : 0),
                            hipMemcpyHostToDevice, st));
     hipEvent_t ev[2] = {nullptr, nullptr};
@@ -874,17 +893,9 @@ heom_status resident_run(const heom_hierarchy* h, const heom::Job& j, const heom
         for (auto& e : ev) HIP_TRY(hipEventCreate(&e));
     if (timed) HIP_TRY(hipEventRecord(ev[0], st));
     int64_t launches = 0;
-    for (int64_t step = 0; step < n_steps; step += a.n_steps, ++launches) {
-        a.step0 = step;
-        a.n_steps = std::min(kResidentSteps, n_steps - step);
-        a.chunk = (uint32_t)launches;
-        a.epoch0 = (uint32_t)(4 * step);
-        if (plan.grid) HIP_TRY(hipStreamSynchronize(st));
-        ResidentPermit permit(plan.grid);
-        hipError_t e = heom::launch_resident(j, a, plan, h->d.precision, st);
-        if (e != hipSuccess) return fail(HEOM_E_DEVICE, "resident launch: %s", hipGetErrorString(e));
-        if (plan.grid) HIP_TRY(hipStreamSynchronize(st));
-    }
+    HIP_TRY(resident_launches(a, plan.grid, n_steps, st, &launches, [&] {
+        return heom::launch_resident(j, a, plan, h->d.precision, st);
+    }));
     if (timed) HIP_TRY(hipEventRecord(ev[1], st));
     alignas(8) char back[768];
     HIP_TRY(hipMemcpyAsync(back, w, sizeof back, hipMemcpyDeviceToHost, st));
@@ -1169,11 +1180,38 @@ heom_status heom_propagate_block(const heom_hierarchy* h, void* state, void* wor
     double* rec = reinterpret_cast<double*>(w + 256 + 3 * copy);
     const int64_t n_rec = heom_record_count(n_steps, record_every);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    HIP_TRY(hipMemsetAsync(status, 0, 4, st));
+    // status at 0, steps done at 8, commit word at 16
+    HIP_TRY(hipMemsetAsync(status, 0, 24, st));
+    hipError_t e = hipSuccess;
+    int64_t done = 0;
+    heom::ResidentPlan plan;
+    if (n_steps > 0 && heom::resident_block_plan(h->t, (int)h->d.n_low, &plan) &&
+        (!plan.grid || copy >= kResidentFlagBytes)) {
+        heom::ResidentArgs a{};
+        a.commit = reinterpret_cast<uint32_t*>(w + 16);
+        a.exch[0] = arr[1];
+        a.exch[1] = arr[2];
+        a.flags = static_cast<uint32_t*>(arr[3]);
+        if (plan.grid) HIP_TRY(hipMemsetAsync(a.flags, 0, kResidentFlagBytes, st));
+        const heom::BlockRun run{state, dt_fs, rec, status, reinterpret_cast<int64_t*>(w + 8), n_rec, record_every};
+        heom::BlockObs ob{};
+        for (int p = 0; p < 3; ++p) std::copy(obs + p * N, obs + (p + 1) * N, ob.v[p]);
+        int64_t launches = 0;
+        HIP_TRY(resident_launches(a, plan.grid, n_steps, st, &launches, [&] {
+            return heom::launch_resident_block(h->t, a, run, ob, plan, st);
+        }));
+        if (plan.grid) {
+            HIP_TRY(hipMemcpyAsync(&done, w + 8, 8, hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
+        } else {
+            done = n_steps;  // one workgroup waits for nobody
+        }
+    }
+    // the rest (all of it, for a hierarchy that does not fit) stage by stage
     heom::StageSpec sp[4];
     heom::rk4_stage_specs(sp);
-    hipError_t e = heom::launch_block_record(state, obs, N, rec, status, st);
-    for (int64_t step = 0; e == hipSuccess && step < n_steps; ++step) {
+    if (done == 0) e = heom::launch_block_record(state, obs, N, rec, status, st);
+    for (int64_t step = done; e == hipSuccess && step < n_steps; ++step) {
         for (int k = 0; k < 4 && e == hipSuccess; ++k) {
             const void* base[3];
             for (int m = 0; m < sp[k].nbase; ++m) base[m] = arr[sp[k].base[m]];

@@ -117,6 +117,7 @@ constexpr int kResidentFlagStride = 16;
 constexpr size_t kResidentFlagBytes = 256 * kResidentFlagStride * 4;
 struct ResidentArgs {
     int32_t groups, slots, low_slots, bulk_threads;  // from the plan
+    int32_t members;              // workgroups of the launch
     int64_t n_steps, step0;       // steps of this launch, and those done before it
     void* exch[2];                // stage outputs in turn: [n_ado-1][N][N]
     void* s0x[2];                 // the same for sigma_0: complex128 [N][N]
@@ -129,6 +130,22 @@ struct ResidentArgs {
 bool resident_plan(const Job& j, int tsize, ResidentPlan* plan);
 hipError_t launch_resident(const Job& j, const ResidentArgs& args, const ResidentPlan& plan,
                            int precision, hipStream_t stream);
+// The coherence-block form the same way.
+struct BlockRun {
+    void* state;                  // complex128 [n_ado][N][3]
+    double dt;
+    double* rec;                  // [n_rec][6]
+    int32_t* status;
+    int64_t* step;
+    int64_t n_rec;
+    int32_t rec_every;
+};
+struct BlockObs {
+    double v[3][kMaxStates];
+};
+bool resident_block_plan(const Tables& t, int n_low, ResidentPlan* plan);
+hipError_t launch_resident_block(const Tables& t, const ResidentArgs& args, const BlockRun& run,
+                                 const BlockObs& obs, const ResidentPlan& plan, hipStream_t stream);
 
 // Launch-shape caps (heom_set_launch_shape; 0 = none).
 extern std::atomic<int> g_max_workgroups, g_max_ados_per_tile;

@@ -162,7 +162,7 @@ struct GridBarrier {
                    : seen;
     }
     __device__ bool wait(uint32_t epoch) const {
-        if ((int)threadIdx.x < A.groups + 1) {
+        if ((int)threadIdx.x < A.members) {
             const gcptr<uint32_t> f = G((const uint32_t*)A.flags + kResidentFlagStride * threadIdx.x);
             const uint64_t t0 = wall_clock64();
             for (uint32_t n = 1;; ++n) {
@@ -618,6 +618,260 @@ hipError_t launch_h(const Job& J, const ResidentArgs& A, const ResidentPlan& p, 
                       : launch_t<T, HC, false, 2>(J, A, p, stream);
 }
 
+// --------------------------------------------------------------------------
+// The coherence-block form of an absorption run (heom_propagate_block, see
+// k_block_stage for the equations) in one launch: the same two forms, FP64,
+// elements (u, a, p), ADO 0 among them.  An element couples to elements of
+// the same row and direction only, so nothing is staged: each link is one
+// load of the element's own (three directions, 48 bytes, per ADO row).
+// Every operation and its order are those of block_stage_elem, so a run
+// gives the bits that the server's batched stages give.
+// --------------------------------------------------------------------------
+struct BlockLds {
+    size_t h, s, wt, off, gam, delta, count, total;
+};
+
+__host__ __device__ inline BlockLds block_lds(int N, int W, int D, int slots, int low, bool hc) {
+    const size_t NN = (size_t)N * N, S = slots;
+    // an ADO has at most D "-" rows and W "+" rows, each of three elements
+    const size_t links = 3 * (S * (D > 0 ? D : 1) + (size_t)low * W);
+    BlockLds L{};
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o = align16(o + bytes);
+        return at;
+    };
+    L.h = take(NN * (hc ? 16 : 8));
+    L.s = take(S * N * 3 * 16);
+    L.wt = take(links * 16);
+    L.off = take(links * 4);
+    L.gam = take(S * 8);
+    L.delta = take((size_t)N * 8);
+    L.count = take(4);
+    L.total = o;
+    return L;
+}
+
+template <bool HC, bool GRID, int EPT>
+__global__ __launch_bounds__((resident_threads<GRID, EPT>())) __attribute__((
+    amdgpu_waves_per_eu(resident_waves<GRID, EPT>()))) void k_resident_block(Tables t, ResidentArgs A,
+                                                                             BlockRun B, BlockObs obs) {
+    extern __shared__ __align__(16) char smem[];
+    __shared__ __align__(16) int dead;
+    const GridBarrier bar{A, &dead};
+    const int tid = threadIdx.x, n_t = blockDim.x;
+    if (tid == 0) dead = GRID && bar.word() == kResidentAborted ? 1 : 0;
+    __syncthreads();
+    if (dead) return;
+    const int N = t.N, W = t.W, D = t.D, Dm = D > 0 ? D : 1, R = 3 * N;
+    const int Gr = GRID ? A.groups : 1, w = GRID ? (int)blockIdx.x : 0;
+    const int ns = max(0, (t.n_ado - 1 - w + Gr) / Gr);
+    const BlockLds L = block_lds(N, W, D, A.slots, A.low_slots, HC);
+    double* sH = reinterpret_cast<double*>(smem + L.h);
+    double* S = reinterpret_cast<double*>(smem + L.s);
+    double* sWt = reinterpret_cast<double*>(smem + L.wt);
+    uint32_t* sOff = reinterpret_cast<uint32_t*>(smem + L.off);
+    double* sGam = reinterpret_cast<double*>(smem + L.gam);
+    double* sDelta = reinterpret_cast<double*>(smem + L.delta);
+    int* sCount = reinterpret_cast<int*>(smem + L.count);
+    for (int e = tid; e < N * N; e += n_t) {
+        sH[HC ? 2 * e : e] = G(t.h_re)[e];
+        if constexpr (HC) sH[2 * e + 1] = G(t.h_im)[e];
+    }
+    for (int g = tid; g < ns; g += n_t) sGam[g] = G(t.damping)[w + g * Gr];
+    for (int x = tid; x < N; x += n_t) sDelta[x] = G(t.delta_state)[x];
+    if (tid == 0) *sCount = 0;
+    __syncthreads();
+    cpx<double> y[EPT], y2[EPT], y3[EPT];
+    int place[EPT], list[EPT];  // slot << 16 | row in the ADO, -1 without one; list begin << 8 | entries
+    uint32_t glob[EPT];
+#pragma unroll
+    for (int q = 0; q < EPT; ++q) {
+        const int e = tid + n_t * q;
+        y[q] = y2[q] = y3[q] = {0.0, 0.0};
+        place[q] = -1;
+        list[q] = 0;
+        glob[q] = 0;
+        if (e >= ns * R) continue;
+        const int g = e / R, r = e - g * R, a = r / 3;
+        const size_t u = w + (size_t)g * Gr;
+        glob[q] = (uint32_t)(u * R + r);
+        y[q] = ld<double>(B.state, glob[q]);
+        sst(S, e, y[q]);
+        const int bi = G(t.state_mode_begin)[a];
+        const int np = G(t.level)[u] < D ? G(t.state_mode_begin)[a + 1] - bi : 0;
+        int n = np;
+        for (int k = 0; k < Dm; ++k) n += G(t.mlist_site)[u * Dm + k] == a;
+        int at = atomicAdd(sCount, n);
+        place[q] = g << 16 | r;
+        list[q] = at << 8 | n;
+        for (int m = 0; m < np; ++m, ++at) {
+            const int l = G(t.state_modes)[bi + m];
+            sOff[at] = (uint32_t)(G(t.plus)[u * W + l] * R + r);
+            sst(sWt, at, cpx<double>{0.0, G(t.plus_w)[u * W + l]});
+        }
+        for (int k = 0; k < Dm; ++k) {
+            if (G(t.mlist_site)[u * Dm + k] != a) continue;
+            const pair_d v = G(reinterpret_cast<const pair_d*>(t.mlist_w))[u * Dm + k];
+            sOff[at] = (uint32_t)(G(reinterpret_cast<const pair_i*>(t.mlist))[u * Dm + k].x * R + r);
+            sst(sWt, at++, cpx<double>{v.x, v.y});
+        }
+    }
+    __syncthreads();
+    // P_p = sum_a obs[p][a] Y_0[a][p] by three threads of ADO 0's workgroup
+    auto record = [&](int64_t slot) {
+        if (w != 0 || tid >= 3 || slot < 0 || slot >= B.n_rec) return;
+        double pr = 0.0, pi = 0.0;
+        for (int a = 0; a < N; ++a) {
+            const cpx<double> x = sld<double>(S, a * 3 + tid);
+            pr = fma(obs.v[tid][a], x.re, pr);
+            pi = fma(obs.v[tid][a], x.im, pi);
+        }
+        G(B.rec)[6 * slot + 2 * tid] = pr;
+        G(B.rec)[6 * slot + 2 * tid + 1] = pi;
+        if (!(isfinite(pr) && isfinite(pi))) *G(B.status) = 1;
+    };
+    if (A.step0 == 0) record(0);
+    const uint32_t x_bytes = (uint32_t)((size_t)t.n_ado * R * 16);
+    bool ok = true;
+    uint32_t epoch = A.epoch0;
+    int rec_left = B.rec_every - (int)(A.step0 % B.rec_every);
+    int64_t rec_slot = A.step0 / B.rec_every;
+    for (int64_t step = 0; ok && step < A.n_steps; ++step) {
+#pragma unroll 1
+        for (int k = 0; k < 4; ++k) {
+            const bool first = step == 0 && k == 0, last = step + 1 == A.n_steps && k == 3;
+            const double h = B.dt * (k < 2 ? 0.5 : k == 2 ? 1.0 : 1.0 / 6.0);
+            const Exchanged xin(first ? B.state : A.exch[(k + 1) & 1], x_bytes);
+            auto fetch = [&](uint32_t o) { return GRID ? xin.template load<double>(o) : sld<double>(S, o); };
+#pragma unroll
+            for (int q = 0; q < EPT; ++q) asm volatile("" : "+v"(place[q]), "+v"(list[q]), "+v"(glob[q]));
+            cpx<double> out[EPT];
+#pragma unroll
+            for (int q = 0; q < EPT; ++q) {
+                out[q] = {0.0, 0.0};
+                if (place[q] < 0) continue;
+                constexpr int KB = 4;  // links in flight
+                const int n = list[q] & 255;
+                const uint32_t* loff = sOff + (list[q] >> 8);
+                const double* lwt = sWt + 2 * (list[q] >> 8);
+                cpx<double> xs[KB];
+#pragma unroll
+                for (int m = 0; m < KB; ++m) {
+                    xs[m] = {0.0, 0.0};
+                    if (m < n) xs[m] = fetch(loff[m]);
+                }
+                const int g = place[q] >> 16, r = place[q] & 0xffff, a = r / 3, p = r - 3 * a;
+                const double* Sg = S + 2 * g * R;
+                const cpx<double> y0 = sld<double>(Sg, r);
+                double cr = t.h_shift * y0.re, ci = t.h_shift * y0.im;
+#pragma unroll 2
+                for (int b = 0; b < N; ++b) {
+                    const cpx<double> v = sld<double>(Sg, 3 * b + p);
+                    if constexpr (HC) {
+                        const cpx<double> hh = sld<double>(sH, a * N + b);
+                        cr = fma(hh.re, v.re, fma(-hh.im, v.im, cr));
+                        ci = fma(hh.re, v.im, fma(hh.im, v.re, ci));
+                    } else {
+                        const double hr = sH[a * N + b];
+                        cr = fma(hr, v.re, cr);
+                        ci = fma(hr, v.im, ci);
+                    }
+                }
+                const double gm = sGam[g] + sDelta[a];
+                double fr = fma(-gm, y0.re, ci), fi = fma(-gm, y0.im, -cr);
+                auto add = [&](int m, cpx<double> x) {
+                    const cpx<double> wt = sld<double>(lwt, m);
+                    fr = fma(wt.re, x.re, fma(-wt.im, x.im, fr));
+                    fi = fma(wt.re, x.im, fma(wt.im, x.re, fi));
+                };
+#pragma unroll
+                for (int m = 0; m < KB; ++m)
+                    if (m < n) add(m, xs[m]);
+#pragma unroll 1
+                for (int m = KB; m < n; ++m) add(m, fetch(loff[m]));
+                const double w_in = k == 0 ? 1.0 : k == 3 ? 1.0 / 3.0 : 0.0;
+                double yr = fma(h, fr, w_in * y0.re), yi = fma(h, fi, w_in * y0.im);
+                if (k == 1 || k == 2) {
+                    yr = fma(1.0, y[q].re, yr);
+                    yi = fma(1.0, y[q].im, yi);
+                } else if (k == 3) {
+                    yr = fma(2.0 / 3.0, y3[q].re, fma(1.0 / 3.0, y2[q].re, fma(-1.0 / 3.0, y[q].re, yr)));
+                    yi = fma(2.0 / 3.0, y3[q].im, fma(1.0 / 3.0, y2[q].im, fma(-1.0 / 3.0, y[q].im, yi)));
+                }
+                out[q] = {yr, yi};
+            }
+            __syncthreads();  // every thread has read this stage's LDS
+#pragma unroll
+            for (int q = 0; q < EPT; ++q) {
+                if (place[q] < 0) continue;
+                sst(S, tid + n_t * q, out[q]);
+                if constexpr (GRID) {
+                    if (!last) Exchanged(A.exch[k & 1], x_bytes).template store<double>(glob[q], out[q]);
+                }
+                if (k == 0) y2[q] = out[q];
+                else if (k == 1) y3[q] = out[q];
+                else if (k == 3) y[q] = out[q];
+            }
+            bool due = false;
+            if (k == 3 && --rec_left == 0) {
+                rec_left = B.rec_every;
+                ++rec_slot;
+                due = true;
+            }
+            ++epoch;
+            if constexpr (GRID) {
+                bar.arrive(epoch);
+                if (due) record(rec_slot);
+                ok = bar.wait(epoch);
+                if (!ok) break;
+            } else {
+                __syncthreads();
+                if (due) record(rec_slot);
+            }
+        }
+    }
+    if constexpr (GRID) {
+        if (tid == 0 && ok) dead = bar.decide(A.chunk + 1) == kResidentAborted ? 1 : 0;
+        __syncthreads();
+        if (!ok || dead) return;
+    }
+#pragma unroll
+    for (int q = 0; q < EPT; ++q)
+        if (place[q] >= 0) st<double>(B.state, glob[q], y[q]);
+    if (w == 0 && tid == 0) {
+        *G(B.step) = A.step0 + A.n_steps;
+        if (!GRID) *G(A.commit) = A.chunk + 1;
+    }
+}
+
+template <bool HC, bool GRID, int EPT>
+hipError_t launch_block_t(const Tables& t, const ResidentArgs& A, const BlockRun& B, const BlockObs& obs,
+                          const ResidentPlan& p, hipStream_t stream) {
+    static std::once_flag once;
+    static hipError_t err = hipSuccess;
+    std::call_once(once, [&] {
+        err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_resident_block<HC, GRID, EPT>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOneLds);
+    });
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL((k_resident_block<HC, GRID, EPT>), dim3(p.groups), dim3(p.threads), p.lds, stream, t, A,
+                       B, obs);
+    return hipGetLastError();
+}
+
+template <bool HC>
+hipError_t launch_block_h(const Tables& t, const ResidentArgs& A, const BlockRun& B, const BlockObs& obs,
+                          const ResidentPlan& p, hipStream_t stream) {
+    if (!p.grid)
+        return p.ept == 1 ? launch_block_t<HC, false, 1>(t, A, B, obs, p, stream)
+                          : launch_block_t<HC, false, 2>(t, A, B, obs, p, stream);
+    return p.ept == 1   ? launch_block_t<HC, true, 1>(t, A, B, obs, p, stream)
+           : p.ept == 2 ? launch_block_t<HC, true, 2>(t, A, B, obs, p, stream)
+                        : launch_block_t<HC, true, 4>(t, A, B, obs, p, stream);
+}
+
 constexpr int round64(int x) { return (x + 63) / 64 * 64; }
 
 }  // namespace
@@ -671,10 +925,51 @@ hipError_t launch_resident(const Job& J, const ResidentArgs& args, const Residen
     A.slots = p.slots;
     A.low_slots = p.low_slots;
     A.bulk_threads = p.bulk_threads;
+    A.members = p.groups + 1;
     const bool hc = J.t.h_complex != 0;
     if (precision == 0)
         return hc ? launch_h<double, true>(J, A, p, stream) : launch_h<double, false>(J, A, p, stream);
     return hc ? launch_h<float, true>(J, A, p, stream) : launch_h<float, false>(J, A, p, stream);
+}
+
+// The same choice for the coherence-block form (elements n_ado * 3 N).
+bool resident_block_plan(const Tables& t, int n_low, ResidentPlan* p) {
+    const int R = 3 * t.N, n = t.n_ado;
+    if (t.W + t.D > 255) return false;
+    const int64_t elements = (int64_t)n * R;
+    const bool hc = t.h_complex != 0;
+    *p = ResidentPlan{};
+    if (elements <= 2 * 1024) {
+        p->lds = block_lds(t.N, t.W, t.D, n, n_low + 1, hc).total;
+        if (p->lds <= kOneLds) {
+            p->groups = 1;
+            p->slots = n;
+            p->low_slots = n_low + 1;
+            p->ept = elements <= 1024 ? 1 : 2;
+            p->threads = round64((int)((elements + p->ept - 1) / p->ept));
+            return true;
+        }
+    }
+    p->grid = true;
+    p->groups = std::min(n, kGridMax);
+    p->slots = (n + p->groups - 1) / p->groups;
+    p->low_slots = (n_low + p->groups) / p->groups;  // of ADOs 0..n_low
+    const int per = (int)std::min<int64_t>((int64_t)p->slots * R, 1 << 20);
+    if (per > 4 * 512) return false;
+    p->lds = block_lds(t.N, t.W, t.D, p->slots, p->low_slots, hc).total;
+    p->ept = per <= resident_threads<true, 1>() ? 1 : per <= 2 * resident_threads<true, 2>() ? 2 : 4;
+    p->threads = std::max(round64((per + p->ept - 1) / p->ept), kGridMax);
+    return p->lds <= kGridLds;
+}
+
+hipError_t launch_resident_block(const Tables& t, const ResidentArgs& args, const BlockRun& run,
+                                 const BlockObs& obs, const ResidentPlan& p, hipStream_t stream) {
+    ResidentArgs A = args;
+    A.groups = A.members = p.groups;
+    A.slots = p.slots;
+    A.low_slots = p.low_slots;
+    return t.h_complex != 0 ? launch_block_h<true>(t, A, run, obs, p, stream)
+                            : launch_block_h<false>(t, A, run, obs, p, stream);
 }
 
 }  // namespace heom

@@ -152,3 +152,51 @@ def test_resident_runs_of_several_threads(heom):
         t.join()
     for a, b in zip(alone, got):
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+def _block_problem(N, M, D, hc, seed):
+    """Excited block in its own frame (zero mean energy), three dipole vectors."""
+    prob = hi.random_problem(seed, N, M=M, D=D, complex_h=hc)
+    prob["H"] = prob["H"] - np.mean(np.diag(prob["H"]).real) * np.eye(N)
+    return prob, np.random.default_rng(seed).normal(size=(3, N))
+
+
+# 60 and 1890 elements, and 62 ADOs whose first has 61 "+" entries, in one
+# workgroup; grids of 252, 783 (two per thread) and 1260 (four) per workgroup
+@pytest.mark.parametrize("size", [(2, 0, 3, False), (5, 0, 4, False), (1, 60, 1, False),
+                                  (7, 1, 4, True), (9, 1, 4, False), (10, 1, 4, False)], ids=str)
+def test_resident_block_matches_stages(heom, orc, size):
+    """The coherence-block run in one launch gives the bits of the stage
+    kernels (a grid that gives up its waits is finished by them); the
+    one-workgroup sizes, which wait for nobody, are held to the oracle."""
+    N, M, D, hc = size
+    _case("resident block", size)
+    prob, mu = _block_problem(N, M, D, hc, 900 + N)
+    lib = heom.load()
+    lib.heom_test_resident_wait.argtypes = [ctypes.c_int64]
+    lib.heom_test_resident_wait.restype = None
+    dt = 0.005 if M > 1 else 0.5
+    h = heom.Hierarchy(prob, 0)
+    out = []
+    for ticks in (-1, 0):
+        y = h.block_state(mu)
+        lib.heom_test_resident_wait(ticks)
+        try:
+            P = h.propagate_block(y, dt, 7, 2, mu)
+        finally:
+            lib.heom_test_resident_wait(-1)
+        out.append((P, y.cpu().numpy()))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    if N > 5:
+        return
+    H = np.zeros((N + 1, N + 1), prob["H"].dtype)
+    H[1:, 1:] = prob["H"]
+    full = dict(prob, H=H, baths=[dict(b, state=b["state"] + 1) for b in prob["baths"]])
+    for p in range(3):
+        m = np.concatenate([[0.0], mu[p]])
+        rho = np.zeros((N + 1, N + 1), complex)
+        rho[:, 0] = m
+        y, rec = orc.propagate(full, orc.initial_state(full, h.n_ado, rho), dt, 7, 2,
+                               {"kind": "dipole", "mu": m, "ground": 0})
+        assert np.max(np.abs(out[0][0][:, p] - (rec[:, 0] + 1j * rec[:, 1]))) <= 1e-12 * np.max(np.abs(rec))
+        assert np.max(np.abs(out[0][1][:, :, p] - y[:, 1:, 0])) <= 1e-12 * max(1.0, np.max(np.abs(y)))
