@@ -917,6 +917,19 @@ heom_status resident_run(const heom_hierarchy* h, const heom::Job& j, const heom
     return HEOM_OK;
 }
 
+// Elements of the ADO array from which a Hermitian run is packed.  Below,
+// the extra launches ("+" sums, pack, unpack) and one wavefront per ADO cost
+// more than the halved bytes give (us per step, complex / packed: FP32 40
+// states, 3321 ADOs 244 / 285, 24 states, 20475 ADOs 323 / 304, 48 states,
+// 20825 ADOs 1208 / 861; FP64 24 states, 2925 ADOs 143 / 151, 17 states, 7770
+// ADOs 264 / 191; packed storage, 33 states, 595 ADOs 108 / 163 and 31
+// states, 2016 ADOs 202 / 149).
+thread_local int64_t t_packed_min = -1;  // this thread's bound instead, for tests
+int64_t packed_min(int precision) {
+    if (t_packed_min >= 0) return t_packed_min;
+    return precision == HEOM_FP64 ? 2000000 : precision == HEOM_FP32_HERM ? 1000000 : 8000000;
+}
+
 // heom_propagate on a given workspace.  `timing` allows the benchmark event
 // timing (which creates HIP events) and `graphs` the step graph (which
 // allocates); the no-alloc entry point passes false for both.
@@ -947,6 +960,7 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     const int N = h->t.N;
     const int rd = heom_record_doubles(N, kind);
     const int64_t n_rec = heom_record_count(n_steps, record_every);
+    const size_t records_bytes = align256((size_t)n_rec * rd * 8);
     char* w = static_cast<char*>(work_dev);
     heom::Job j = heom::bind_workspace(h, io, w, dt_fs, n_steps, record_every, kind,
                                        kind == HEOM_OBS_DIPOLE ? obs->ground : 0, hermitian);
@@ -978,7 +992,29 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     heom::StageSpec sp[4];
     heom::rk4_stage_specs(sp);
 
-    if (h->d.precision == HEOM_FP32_HERM && j.n_low > 0 && tiles > 0) {
+    // large Hermitian runs keep their ADOs packed between the first and the
+    // last step
+    heom::PackedLayout lay;
+    heom::PackedRun pack{};
+    const int64_t elements = (int64_t)(h->t.n_ado - 1) * N * N;
+    const bool packed = n_steps > 0 && tiles > 0 && elements >= packed_min(h->d.precision) && heom::packed_plan(j, h->d.precision, h->info.sigma0_bytes, need - records_bytes,
+                                          heom::control_bytes(N), &lay);
+    if (packed) {
+        for (int k = 0; k < 3; ++k) {
+            j.sig0[k + 1] = w + lay.sig0[k];
+            if (k < 2) j.rest[k + 1] = w + lay.array[k];
+            if (k < 2) pack.mirror[k] = w + lay.mirror[k];
+            if (k < 2 && lay.side[k]) pack.side[k] = w + lay.side[k];
+        }
+        j.rest[3] = j.rest[1];
+        pack.z = w + lay.array[2];
+        if (lay.y) {
+            pack.complex_rest = io.rest;
+            j.rest[0] = w + lay.y;
+        }
+        hipError_t e = heom::packed_begin(j, pack, h->d.precision, st);
+        if (e != hipSuccess) return fail(HEOM_E_DEVICE, "pack launch: %s", hipGetErrorString(e));
+    } else if (h->d.precision == HEOM_FP32_HERM && j.n_low > 0 && tiles > 0) {
         // complex copies of the lower levels, alternating between the two
         // buffers: stage k reads the copy the previous stage wrote
         hipError_t e = heom::launch_pk_mirror(io.rest, j.mirror[0], N, j.n_low, st);
@@ -996,9 +1032,16 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     static const int kPasses[4] = {2, 3, 3, 5};
     auto launch_step = [&](int64_t step, hipStream_t s) -> hipError_t {
         for (int k = 0; k < 4; ++k) {
-            hipError_t e = heom::launch_stage(j, nullptr, 0, tiles, h->d.precision, sp[k], s,
-                                              timed ? ev[2 * (step * 4 + k)] : nullptr,
-                                              timed ? ev[2 * (step * 4 + k) + 1] : nullptr);
+            const hipEvent_t begin = timed ? ev[2 * (step * 4 + k)] : nullptr;
+            const hipEvent_t end = timed ? ev[2 * (step * 4 + k) + 1] : nullptr;
+            hipError_t e = hipSuccess;
+            if (packed) {
+                if (begin) e = hipEventRecord(begin, s);
+                if (e == hipSuccess) e = heom::packed_stage(k, j, pack, h->d.precision, sp[k], s);
+                if (e == hipSuccess && end) e = hipEventRecord(end, s);
+            } else {
+                e = heom::launch_stage(j, nullptr, 0, tiles, h->d.precision, sp[k], s, begin, end);
+            }
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -1028,6 +1071,10 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
         if (e != hipSuccess)
             return fail(HEOM_E_DEVICE, "stage launch (%s): %s", heom::last_launch_failure(),
                         hipGetErrorString(e));
+    }
+    if (packed) {
+        hipError_t e = heom::packed_end(j, pack, h->d.precision, st);
+        if (e != hipSuccess) return fail(HEOM_E_DEVICE, "unpack launch: %s", hipGetErrorString(e));
     }
     if (n_steps == 0) {
         // record the initial state only: a stage-1 pass into slot 1 does it
@@ -1073,6 +1120,10 @@ heom_status heom_propagate(const heom_hierarchy* h, heom_state io, void* work_de
 // Not part of the ABI: bounds the waits of this thread's resident launches
 // (100 MHz ticks; 0 = the first unanswered poll gives up, < 0 = the default).
 void heom_test_resident_wait(int64_t ticks) { t_resident_wait_ticks = ticks; }
+
+// Not part of the ABI: runs of this thread are packed from so many elements
+// on (< 0 = the library's choice).
+void heom_test_packed_min(int64_t elements) { t_packed_min = elements; }
 
 heom_status heom_propagate_noalloc(const heom_hierarchy* h, heom_state io, double dt_fs,
                                    int64_t n_steps, int32_t record_every,

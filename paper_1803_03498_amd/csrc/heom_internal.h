@@ -147,6 +147,29 @@ bool resident_block_plan(const Tables& t, int n_low, ResidentPlan* plan);
 hipError_t launch_resident_block(const Tables& t, const ResidentArgs& args, const BlockRun& run,
                                  const BlockObs& obs, const ResidentPlan& plan, hipStream_t stream);
 
+// Propagation of Hermitian ADOs in packed form (heom_packed.hip).
+struct PackedLayout {             // offsets into the propagation workspace
+    size_t sig0[3], array[3], mirror[2];
+    size_t y;                     // packed copy of a complex state (0: the state is packed)
+    size_t side[2];               // 0: no room
+};
+struct PackedRun {
+    void* z;                      // (-y + Y2 + 2 Y3)/3
+    void* mirror[2];              // planes of the ADOs 1..n_low, of stage inputs in turn
+    void* side[2];                // coupling rows of the top level, of stage inputs in turn, or null
+    void* complex_rest;           // the caller's complex ADOs, null if packed
+};
+bool packed_plan(const Job& j, int precision, size_t sigma0_bytes, size_t work_bytes, size_t offset,
+                 PackedLayout* layout);
+// Packs the state (Job::rest[0] from complex_rest), runs stage k of a step
+// (Job::rest: y, Y2, Y3, Y4 = Y2), unpacks it.
+hipError_t packed_begin(const Job& j, const PackedRun& r, int precision, hipStream_t stream);
+hipError_t packed_stage(int k, const Job& j, const PackedRun& r, int precision, const StageSpec& sp,
+                        hipStream_t stream);
+hipError_t packed_end(const Job& j, const PackedRun& r, int precision, hipStream_t stream);
+// The sigma_0 stage next to packed ADOs, in a launch of its own.
+hipError_t launch_sigma0_packed(const Job& j, int tsize, const StageSpec& sp, hipStream_t stream);
+
 // Launch-shape caps (heom_set_launch_shape; 0 = none).
 extern std::atomic<int> g_max_workgroups, g_max_ados_per_tile;
 

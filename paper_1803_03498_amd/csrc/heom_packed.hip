@@ -1,0 +1,742 @@
+// Propagation of Hermitian ADOs in packed form (real H, 17 <= N <= 64,
+// HEOM_FP32_MIXED, HEOM_FP64 and HEOM_FP32_HERM): eq. HEOM of the section
+// "HEOM formalism" of Kramer et al., arXiv:1803.03498, fused with RK4.
+//
+// A Hermitian matrix is half redundant, and these runs are bound by the bytes
+// of the ADO array.  Inside a propagation every ADO u >= 1 is kept as the real
+// N x N array P, P[i][j] = Re sigma(i, j) for i <= j and Im sigma(j, i) for
+// i > j (the storage of HEOM_FP32_HERM); complex states are packed before the
+// first step and unpacked after the last (3 passes over the complex array per
+// run).  A step moves 12 passes over P, half the bytes of the complex form
+// each:
+//   1: Y2 = y + dt/2 f(y)                                    read 1, write 1
+//   2: Y3 = y + dt/2 f(Y2), Z = (-y + Y2 + 2 Y3)/3            read 2, write 2
+//   3: Y4 = y + dt f(Y3)            (over Y2)                read 2, write 1
+//   4: y' = Y4/3 + Z + dt/6 f(Y4)                            read 2, write 1
+//
+// One wavefront computes one ADO, with no barrier anywhere.  With sigma = A + iB
+// (A symmetric, B antisymmetric)
+//   Re(-i[H, sigma]) = H B - B H,    Im(-i[H, sigma]) = -(H A - A H),
+// and only half of each is needed: 16 x 16 tiles (I, J) with I >= J of the
+// real part, I <= J of the imaginary one.  A tile
+//   T_IJ = sum_K +-H_IK X_KJ -+ X_IK H_KJ
+// is two matrix-core products per K and k-step.  X_IK as the A operand has
+// the registers of X_KI as the B operand (X^T = +-X, and H is symmetric), so
+// the tiles (K, J), all J, serve both, and nothing is transposed through
+// memory between product and result.  That is 4/3 of the multiplications of
+// H sigma alone; in return there is no second pair of LDS planes and no
+// barrier, whose latency held the complex kernel at 1.5 ms per stage at 48
+// sites however few bytes the stage moved.
+//
+// Global accesses are linear (P as it lies in memory, 16 bytes per lane): the
+// tile goes to this wavefront's own LDS tile, operands and results use that.
+// (Operands straight from memory took 2.4 ms per stage at 48 sites: rows 16
+// lanes apart do not coalesce, 2200 L1 accesses per plane.)  Lane (g, c) =
+// (lane / 16, lane % 16) holds X[16K + 4g + r][16J + c], r = 0..3: the k index
+// of a 16x16x4 product is permuted alike in both operands, so that r runs over
+// four products, and an element stored transposed is one 16-byte LDS access
+// for all r.  The output element (16I + 4g + r, 16J + c) belongs at [j][i],
+// again 16 bytes.  (In FP64 the hardware's D rows are 4r + g; columns are
+// permuted by the same map.)  The tile's stride 16 NB + 4 keeps both accesses
+// free of bank conflicts and makes every offset a constant.
+//
+// "-" links ride along as one more product per four links: with E[i][a] =
+// (i == s_a) and the weighted rows R_a, E R + (E R)^dagger.  The rows of the
+// lower-level neighbours come from mirrors: real and imaginary planes, full
+// N x N, of the ADOs below the top level (a few percent), written by every
+// stage.  "+" links exist below the top level only; k_packed_plus sums them
+// into the output slot of those ADOs first, and the stage adds that.  What it
+// reads of a top-level ADO is the row of each of its links; every stage leaves
+// those rows side by side ("side" rows), because a row of a Hermitian matrix
+// is half a row and half a column of P (48 sites: 0.43 ms per stage without).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <atomic>
+#include <mutex>
+
+#include "heom_device.h"
+#include "heom_internal.h"
+#include "heom_stage_common.h"
+
+namespace heom {
+namespace {
+
+template <typename T>
+struct Vec4;
+template <>
+struct Vec4<float> {
+    // element alignment: rows of odd N start anywhere
+    typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <>
+struct Vec4<double> {
+    typedef double type __attribute__((ext_vector_type(4), aligned(8)));
+};
+
+template <typename T>
+struct PackedStage {
+    const T* in;
+    T* out;
+    const T* base;  // y (stages 2, 3) or Z (stage 4)
+    T* z;           // stage 2
+    const T *mr_in, *mi_in;  // mirror planes of `in`, [n_low][N][N]
+    T *mr_out, *mi_out;      // of `out`
+    T* side_out;             // side rows of `out`, complex [top ADO][D][N], or null
+    T w_in, h;
+};
+
+// Wavefronts per SIMD that registers and LDS allow; one workgroup per CU.
+template <typename T, int NB>
+constexpr int packed_waves() {
+    return sizeof(T) == 4 ? (NB == 2 ? 4 : NB == 3 ? 3 : 2) : (NB == 2 ? 2 : 1);
+}
+template <typename T, int NB>
+constexpr int packed_threads() {
+    return 256 * packed_waves<T, NB>();
+}
+// k-steps of the last K block of `rem` columns (1..16): lane group g takes the
+// columns kr g + r, r < kr, so that 8 columns need 2 products, not 4.
+__host__ __device__ constexpr int packed_last_steps(int rem) { return (rem + 3) / 4; }
+template <int NB>
+constexpr int packed_stride() {
+    return 16 * NB + 4;
+}
+// LDS elements: H in operand order, Delta, one tile per wavefront
+template <typename T, int NB>
+constexpr size_t packed_lds() {
+    return sizeof(T) * (NB * NB * 256 + 16 * NB +
+                        (size_t)(packed_threads<T, NB>() / 64) * 16 * NB * packed_stride<NB>());
+}
+
+template <typename T, int NB, bool V4, int NBASE, bool ZOUT>
+__global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
+    amdgpu_waves_per_eu((packed_waves<T, NB>())))) void k_packed(Job J, StageSpec sp, PackedStage<T> A,
+                                                                 int s0_blocks, unsigned lds_total) {
+    extern __shared__ __align__(16) char smem[];
+    if ((int)blockIdx.x < s0_blocks) {
+        // the first workgroup carries the sigma_0 stage along
+        sigma0_stage<T, false, false, true>(J, nullptr, 0, sp, lds_total, smem);
+        return;
+    }
+    using V = typename Vec4<T>::type;
+    typedef T VL __attribute__((ext_vector_type(4)));  // aligned, in LDS
+    using acc_t = typename mfma_acc<T>::type;
+    constexpr int LS = packed_stride<NB>(), TILE = 16 * NB * LS, NT = NB * (NB + 1) / 2;
+    const Tables& t = J.t;
+    const int N = t.N, NN = N * N, Dm = t.D > 0 ? t.D : 1;
+    T* sH = reinterpret_cast<T*>(smem);
+    T* sDelta = sH + NB * NB * 256;
+    T* tiles = sDelta + 16 * NB;
+    for (int x = threadIdx.x; x < NB * NB * 256; x += blockDim.x) {
+        const int r = x & 3, ln = (x >> 2) & 63, ik = x >> 8, I = ik / NB, K = ik - I * NB;
+        const int c = ln & 15, g = ln >> 4, jl = sizeof(T) == 8 ? 4 * (c & 3) + (c >> 2) : c;
+        const int steps = K < NB - 1 ? 4 : packed_last_steps(N - 16 * (NB - 1));
+        const int row = 16 * I + jl, col = 16 * K + steps * g + r;
+        T v = (T)0;  // outside N x N: what the tile holds there meets these zeros
+        if (r < steps && row < N && col < N) {
+            if constexpr (sizeof(T) == 4) v = G(t.h_re_f32)[row * N + col];
+            else v = G(t.h_re)[row * N + col];
+        }
+        sH[x] = v;
+    }
+    for (int x = threadIdx.x; x < 16 * NB; x += blockDim.x) sDelta[x] = x < N ? (T)G(t.delta_state)[x] : (T)0;
+    // the padding of a tile stays zero
+    for (int x = threadIdx.x; x < (int)(blockDim.x / 64) * TILE; x += blockDim.x) tiles[x] = (T)0;
+    __syncthreads();
+
+    const int kr = packed_last_steps(N - 16 * (NB - 1));
+    const int waves = blockDim.x / 64, wave = uniform((int)threadIdx.x >> 6);
+    T* S = tiles + wave * TILE;
+    const int first = 1 + ((int)blockIdx.x - s0_blocks) * waves + wave;
+    const int stride = ((int)gridDim.x - s0_blocks) * waves;
+    int lane = threadIdx.x & 63;
+
+    // linear pieces of P: four elements at 4 (lane + 64 q), q < nq; beyond the
+    // end the last four once more (the same values from several lanes; the
+    // loads are not conditional on q, which would keep undefined values live)
+    constexpr int Q = NB * NB;
+    int nq = (NN + 255) / 256;
+    const uint32_t by_n = 0xFFFFFFFFu / (uint32_t)N + 1u;  // e / N = mulhi(e, by_n) for e < 2^16
+    struct Pieces {
+        V v[Q];
+    };
+    auto first_of = [&](int q) { return min(4 * (lane + 64 * q), NN - 4); };
+    auto load = [&](const T* src, Pieces& p) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            p.v[q] = *reinterpret_cast<gcptr<V>>(G(reinterpret_cast<const char*>(src)) +
+                                                     (uint32_t)first_of(q) * (uint32_t)sizeof(T));
+    };
+    auto store_piece = [&](T* dst, int q, V v) {
+        *reinterpret_cast<gptr<V>>(G(reinterpret_cast<char*>(dst)) + (uint32_t)first_of(q) * (uint32_t)sizeof(T)) = v;
+    };
+    auto lds_at = [&](int e) { return S + (int)__umulhi((uint32_t)e, by_n) * (LS - N) + e; };
+    // four elements from e on: those within `left` in e's row, the rest in the
+    // next (N >= 17, so no more rows)
+    auto lds_row = [&](int e, T*& at, int& left) {
+        const int i = (int)__umulhi((uint32_t)e, by_n);
+        at = S + i * (LS - N) + e;
+        left = N - (e - i * N);
+    };
+    auto piece_to_lds = [&](int q, V v) {
+        if constexpr (V4) {
+            *reinterpret_cast<VL*>(lds_at(first_of(q))) = v;
+        } else {
+            T* at;
+            int left;
+            lds_row(first_of(q), at, left);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) at[r < left ? r : r + LS - N] = v[r];
+        }
+    };
+    auto piece_from_lds = [&](int q) -> V {
+        V v;
+        if constexpr (V4) {
+            v = *reinterpret_cast<const VL*>(lds_at(first_of(q)));
+        } else {
+            T* at;
+            int left;
+            lds_row(first_of(q), at, left);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = at[r < left ? r : r + LS - N];
+        }
+        return v;
+    };
+    // one wavefront's LDS accesses are in order; this keeps the compiler's
+    auto fence = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+
+    // "-" links 4q + g of ADO u: weighted row, columns 16 jb + jl
+    auto link = [&](int u, int q, int& s, T xr[NB], T xi[NB]) {
+        const int c = lane & 15, g = lane >> 4, jl = sizeof(T) == 8 ? 4 * (c & 3) + (c >> 2) : c;
+        const int a = 4 * q + g;
+        const size_t at = (size_t)u * Dm + min(a, Dm - 1);
+        const int nb = a < Dm ? G(reinterpret_cast<const pair_i*>(t.mlist))[at].x : -1;
+        s = nb >= 0 ? G(t.mlist_site)[at] : -1;
+        T ml, mc;
+        if constexpr (sizeof(T) == 4) {
+            const pair_f w = G(reinterpret_cast<const pair_f*>(t.mlist_w32))[at];
+            ml = w.x;
+            mc = w.y;
+        } else {
+            const pair_d w = G(reinterpret_cast<const pair_d*>(t.mlist_w))[at];
+            ml = w.x;
+            mc = w.y;
+        }
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) {
+            const int col = min(16 * jb + jl, N - 1);
+            T re = 0, im = 0;
+            if (nb > 0) {
+                const size_t o = (size_t)(nb - 1) * NN + s * N + col;
+                re = G(A.mr_in)[o];
+                im = G(A.mi_in)[o];
+            } else if (nb == 0) {
+                const cpx<double> v = ld<double>(J.sig0[sp.in], (size_t)s * N + col);
+                re = (T)v.re;
+                im = (T)v.im;
+            }
+            // (ml + i mc) x, the V^o part alone on the diagonal
+            const T m = 16 * jb + jl == s ? (T)0 : mc;
+            xr[jb] = nb >= 0 ? ml * re - m * im : (T)0;
+            xi[jb] = nb >= 0 ? ml * im + m * re : (T)0;
+        }
+    };
+
+    // The next tile and this one's stage base are read ahead where the
+    // registers allow; at 32 < N in FP32 three wavefronts per SIMD cover the
+    // waits instead (the base then goes out before the elementwise part).
+    constexpr bool kAhead = sizeof(T) == 8 || NB == 2;
+    Pieces pre;
+    if constexpr (kAhead) load(A.in + (size_t)(min(first, t.n_ado - 1) - 1) * NN, pre);
+    for (int u = first; u < t.n_ado; u += stride) {
+        // through an empty asm: addresses and conditions hoisted out of the
+        // loop would hold (and spill) a register each
+        asm volatile("" : "+v"(lane), "+s"(nq));
+        const int c = lane & 15, g = lane >> 4;
+        // column (and operand row) of this lane inside a tile
+        const int jl = sizeof(T) == 8 ? 4 * (c & 3) + (c >> 2) : c;
+        const size_t tile = (size_t)(u - 1) * NN;
+        int s0;
+        T xr[NB], xi[NB];
+        Pieces bas;
+        {
+            Pieces p;
+            if constexpr (kAhead) p = pre;
+            else load(A.in + tile, p);
+            link(u, 0, s0, xr, xi);
+            if constexpr (kAhead) {
+                if constexpr (NBASE > 0) load(A.base + tile, bas);
+                load(A.in + (size_t)(min(u + stride, t.n_ado - 1) - 1) * NN, pre);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                if (q < nq) piece_to_lds(q, p.v[q]);
+                if (!V4) __builtin_amdgcn_sched_barrier(0);  // four addresses per piece
+            }
+        }
+        fence();
+        acc_t re[NT], im[NT];  // tiles (a, b) of the real part, (b, a) of the imaginary one, a >= b
+#pragma unroll
+        for (int x = 0; x < NT; ++x) re[x] = im[x] = acc_t{0, 0, 0, 0};
+#pragma unroll
+        for (int K = 0; K < NB; ++K) {
+            // the scheduler would otherwise load every K block's operands first
+            __builtin_amdgcn_sched_barrier(0);
+            const int steps = K < NB - 1 ? 4 : kr, k0 = steps * g;
+            const T* Sd = S + k0 * LS + jl;  // direct: [k0 + r][jl]
+            const T* St = S + jl * LS + k0;  // transposed: [jl][k0 + r]
+            T XA[NB][4], XB[NB][4], HR[NB][4];
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb) {
+                const VL hv = *reinterpret_cast<const VL*>(sH + ((jb * NB + K) * 64 + lane) * 4);
+                T tr[4];
+                if (K < NB - 1) {
+                    const VL v = *reinterpret_cast<const VL*>(St + 16 * jb * LS + 16 * K);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) tr[r] = v[r];
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) tr[r] = St[16 * jb * LS + 16 * K + r];
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    HR[jb][r] = hv[r];
+                    const T d = Sd[(16 * K + r) * LS + 16 * jb];
+                    if (K < jb) {
+                        XA[jb][r] = d;
+                        XB[jb][r] = tr[r];
+                    } else if (K > jb) {
+                        XA[jb][r] = tr[r];
+                        XB[jb][r] = -d;
+                    } else {
+                        const int k = k0 + r;
+                        XA[jb][r] = k < jl ? d : tr[r];
+                        XB[jb][r] = k < jl ? tr[r] : (k > jl ? -d : (T)0);
+                    }
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (r >= steps) break;
+#pragma unroll
+                for (int a = 0; a < NB; ++a)
+#pragma unroll
+                    for (int b = 0; b <= a; ++b) {
+                        const int x = a * (a + 1) / 2 + b;
+                        re[x] = mfma16(HR[a][r], XB[b][r], re[x]);
+                        im[x] = mfma16(HR[b][r], -XA[a][r], im[x]);
+                        re[x] = mfma16(XB[a][r], HR[b][r], re[x]);
+                        im[x] = mfma16(XA[b][r], HR[a][r], im[x]);
+                    }
+            }
+        }
+        // E R + (E R)^dagger, four links at a time
+        for (int q = 0;;) {
+            T E[NB];
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb) E[jb] = s0 == 16 * jb + jl ? (T)1 : (T)0;
+#pragma unroll
+            for (int a = 0; a < NB; ++a)
+#pragma unroll
+                for (int b = 0; b <= a; ++b) {
+                    const int x = a * (a + 1) / 2 + b;
+                    re[x] = mfma16(E[a], xr[b], re[x]);
+                    im[x] = mfma16(E[b], xi[a], im[x]);
+                    re[x] = mfma16(xr[a], E[b], re[x]);
+                    im[x] = mfma16(-xi[b], E[a], im[x]);
+                }
+            if (4 * ++q >= Dm) break;
+            link(u, q, s0, xr, xi);
+        }
+        const bool low = u <= J.n_low;
+        if constexpr (!kAhead && NBASE > 0) load(A.base + tile, bas);
+        // w_in sigma + h (f - damping) at [j][i], in place of sigma
+        const T gam = (T)G(t.damping)[u];
+        fence();
+#pragma unroll
+        for (int rb = 0; rb < NB; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < NB; ++cb) {
+                if (cb == 0) __builtin_amdgcn_sched_barrier(0);
+                const int x = max(rb, cb) * (max(rb, cb) + 1) / 2 + min(rb, cb);
+                const int j = 16 * rb + jl, i0 = 16 * cb + 4 * g;
+                T* at = S + (16 * rb + jl) * LS + 16 * cb + 4 * g;
+                const VL s = *reinterpret_cast<const VL*>(at);
+                const VL di = *reinterpret_cast<const VL*>(sDelta + i0);
+                const T dj = sDelta[j];
+                VL o;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    T f, gm = gam + di[r] + dj;
+                    if (cb > rb) f = re[x][r];
+                    else if (cb < rb) f = im[x][r];
+                    else {
+                        f = 4 * g + r >= jl ? re[x][r] : im[x][r];
+                        if (4 * g + r == jl) gm = gam;
+                    }
+                    o[r] = A.w_in * s[r] + A.h * (f - gm * s[r]);
+                }
+                if (V4 || cb < NB - 1) {
+                    if (j < N && i0 < N) *reinterpret_cast<VL*>(at) = o;
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (j < N && i0 + r < N) at[r] = o[r];
+                }
+            }
+        fence();
+        // linear again: the bases, and what the next stages need
+        __builtin_amdgcn_sched_barrier(0);
+        Pieces own;
+        if constexpr (ZOUT) load(A.in + tile, own);
+        const bool again = low || A.side_out;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (q >= nq) continue;
+            V o = piece_from_lds(q);
+            if (low)
+                o += A.h * *reinterpret_cast<gcptr<V>>(G(reinterpret_cast<const char*>(A.out + tile)) +
+                                                       (uint32_t)first_of(q) * (uint32_t)sizeof(T));
+            if constexpr (NBASE > 0) o += bas.v[q];
+            store_piece(A.out + tile, q, o);
+            // (-y + Y2 + 2 Y3)/3 by increments on 2/3 y
+            if constexpr (ZOUT)
+                store_piece(A.z + tile, q,
+                            (T)(2.0 / 3.0) * bas.v[q] +
+                                (T)(1.0 / 3.0) * ((own.v[q] - bas.v[q]) + (T)2 * (o - bas.v[q])));
+            if (again) piece_to_lds(q, o);
+            if (!V4) __builtin_amdgcn_sched_barrier(0);
+        }
+        if (again) {
+            fence();
+            if (low) {
+                // full planes for the next stage's "-" rows
+                for (int e = lane; e < NN; e += 64) {
+                    const int i = e / N, j = e - i * N;
+                    const T up = S[min(i, j) * LS + max(i, j)], lo = S[max(i, j) * LS + min(i, j)];
+                    G(A.mr_out)[tile + e] = up;
+                    G(A.mi_out)[tile + e] = i < j ? lo : (i > j ? -lo : (T)0);
+                }
+            } else {
+                // the rows that lower levels read of this ADO
+                for (int a = 0; a < Dm; ++a) {
+                    const size_t at = (size_t)u * Dm + a;
+                    const int s = uniform(G(t.mlist_site)[at]);
+                    if (s < 0) break;
+                    if (lane < N) {
+                        const T up = S[min(s, lane) * LS + max(s, lane)], lo = S[max(s, lane) * LS + min(s, lane)];
+                        st<T>(A.side_out, ((size_t)(u - 1 - J.n_low) * Dm + a) * N + lane,
+                              cpx<T>{up, s < lane ? lo : (s > lane ? -lo : (T)0)});
+                    }
+                }
+            }
+            fence();
+        }
+    }
+}
+
+// "+" sums of the ADOs 1..n_low (one per workgroup) into F, in P form: with
+// S_i[j] = sum over the modes l of state i of w_l sigma_{u+e_l}[i][j],
+// i(S_i[j] - conj S_j[i]): Re -(Im S_i[j] + Im S_j[i]), Im Re S_i[j] - Re S_j[i].
+template <typename T>
+__global__ __launch_bounds__(256) void k_packed_plus(Tables t, int n_low, const T* in, const T* mr, const T* mi,
+                                                     const T* side, T* F) {
+    extern __shared__ __align__(16) char smem[];
+    const int N = t.N, NN = N * N, W = t.W, LS = N + 1;
+    T* sA = reinterpret_cast<T*>(smem);
+    T* sB = sA + N * LS;
+    // per mode, in the order of the states: weight, neighbour, side row
+    T* sW = sB + N * LS;
+    int* sNb = reinterpret_cast<int*>(sW + W);
+    int* sRow = sNb + W;
+    int* sBegin = sRow + W;
+    const int u = 1 + blockIdx.x, Dm = t.D;
+    for (int m = threadIdx.x; m < W; m += 256) {
+        const int l = G(t.state_modes)[m], nb = G(t.plus)[(size_t)u * W + l];
+        // the link's place among those of u + e_l: the active modes of u before l
+        int k = 0;
+        for (int a = 0; a < Dm; ++a) {
+            const pair_i v = G(reinterpret_cast<const pair_i*>(t.mlist))[(size_t)u * Dm + a];
+            k += v.x >= 0 && (v.y & 255) < l;
+        }
+        sW[m] = (T)G(t.plus_w)[(size_t)u * W + l];
+        sNb[m] = nb;
+        sRow[m] = (nb - 1 - n_low) * Dm + k;
+    }
+    for (int x = threadIdx.x; x <= N; x += 256) sBegin[x] = G(t.state_mode_begin)[x];
+    __syncthreads();
+    for (int e = threadIdx.x; e < NN; e += 256) {
+        const int i = e / N, j = e - i * N;
+        T re = 0, im = 0;
+#pragma unroll 2
+        for (int m = sBegin[i]; m < sBegin[i + 1]; ++m) {
+            const T w = sW[m];
+            const int nb = sNb[m];
+            const size_t at = (size_t)(nb - 1) * NN;
+            if (nb <= n_low) {
+                re += w * G(mr)[at + e];
+                im += w * G(mi)[at + e];
+            } else if (side) {
+                const cpx<T> v = ld<T>(side, (size_t)sRow[m] * N + j);
+                re += w * v.re;
+                im += w * v.im;
+            } else {
+                const T up = G(in)[at + min(i, j) * N + max(i, j)], lo = G(in)[at + max(i, j) * N + min(i, j)];
+                re += w * up;
+                im += w * (i < j ? lo : -lo);
+            }
+        }
+        sA[i * LS + j] = re;
+        sB[i * LS + j] = im;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < NN; e += 256) {
+        const int i = e / N, j = e - i * N;
+        T f = (T)0;
+        if (i < j) f = -(sB[i * LS + j] + sB[j * LS + i]);
+        else if (i > j) f = sA[j * LS + i] - sA[i * LS + j];  // Im of (j, i)
+        G(F)[(size_t)(u - 1) * NN + e] = f;
+    }
+}
+
+// Complex ADOs <-> P, one ADO per workgroup; packing also fills the mirror
+// planes of the ADOs 1..n_low and the side rows (if any) of the others.
+template <typename T>
+__global__ __launch_bounds__(256) void k_pack(Tables t, const void* rest, T* P, T* mr, T* mi, T* side, int n_low) {
+    extern __shared__ __align__(16) char smem[];
+    T* s = reinterpret_cast<T*>(smem);  // [N][N + 1]
+    const int N = t.N, NN = N * N;
+    const size_t at = (size_t)blockIdx.x * NN;
+    const bool low = (int)blockIdx.x < n_low;
+    for (int e = threadIdx.x; e < NN; e += 256) {
+        const int i = e / N, j = e - i * N;
+        if (j < i) continue;
+        const cpx<T> v = ld<T>(rest, at + e);
+        s[i * (N + 1) + j] = v.re;
+        if (j > i) s[j * (N + 1) + i] = v.im;
+        if (low) {
+            const T im = j > i ? v.im : (T)0;
+            G(mr)[at + e] = G(mr)[at + j * N + i] = v.re;
+            G(mi)[at + e] = im;
+            if (j > i) G(mi)[at + j * N + i] = -im;
+        }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < NN; e += 256) {
+        const int i = e / N;
+        G(P)[at + e] = s[i * (N + 1) + e - i * N];
+    }
+    if (low || !side) return;
+    const int Dm = t.D;
+    for (int x = threadIdx.x; x < Dm * N; x += 256) {
+        const int a = x / N, j = x - a * N;
+        const int r = G(t.mlist_site)[(size_t)(1 + blockIdx.x) * Dm + a];
+        if (r < 0) continue;
+        const T up = s[min(r, j) * (N + 1) + max(r, j)], lo = s[max(r, j) * (N + 1) + min(r, j)];
+        st<T>(side, ((size_t)((int)blockIdx.x - n_low) * Dm + a) * N + j,
+              cpx<T>{up, r < j ? lo : (r > j ? -lo : (T)0)});
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_unpack(const T* P, void* rest, int N) {
+    extern __shared__ __align__(16) char smem[];
+    T* s = reinterpret_cast<T*>(smem);
+    const int NN = N * N;
+    const size_t at = (size_t)blockIdx.x * NN;
+    for (int e = threadIdx.x; e < NN; e += 256) {
+        const int i = e / N;
+        s[i * (N + 1) + e - i * N] = G(P)[at + e];
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < NN; e += 256) {
+        const int i = e / N, j = e - i * N;
+        const T re = s[min(i, j) * (N + 1) + max(i, j)], lo = s[max(i, j) * (N + 1) + min(i, j)];
+        st<T>(rest, at + e, cpx<T>{re, i < j ? lo : (i > j ? -lo : (T)0)});
+    }
+}
+
+// Mirror planes of the packed ADOs 1..n_low.
+template <typename T>
+__global__ __launch_bounds__(256) void k_mirror(const T* P, T* mr, T* mi, int N) {
+    const int NN = N * N;
+    const size_t at = (size_t)blockIdx.x * NN;
+    for (int e = threadIdx.x; e < NN; e += 256) {
+        const int i = e / N, j = e - i * N;
+        const T up = G(P)[at + min(i, j) * N + max(i, j)], lo = G(P)[at + max(i, j) * N + min(i, j)];
+        G(mr)[at + e] = up;
+        G(mi)[at + e] = i < j ? lo : (i > j ? -lo : (T)0);
+    }
+}
+
+hipError_t full_lds(std::once_flag& once, hipError_t& err, const void* fn) {
+    std::call_once(once, [&] {
+        err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    });
+    return err;
+}
+
+template <typename T, int NB, bool V4, int NBASE, bool ZOUT>
+hipError_t launch_t(const Job& J, const StageSpec& sp, const PackedStage<T>& A, hipStream_t stream) {
+    const void* fn = reinterpret_cast<const void*>(&k_packed<T, NB, V4, NBASE, ZOUT>);
+    static std::once_flag once;
+    static hipError_t err = hipSuccess;
+    if (full_lds(once, err, fn) != hipSuccess) return err;
+    constexpr int threads = packed_threads<T, NB>(), waves = threads / 64;
+    const int n = J.t.n_ado - 1, N = J.t.N;
+    // one workgroup per CU; sigma_0 rides along on a CU of its own when its
+    // LDS fits (its rows only if they do)
+    size_t lds = packed_lds<T, NB>();
+    constexpr size_t budget = 160 * 1024;
+    const size_t full = sigma0_lds(N, J.t.W, (int)sizeof(T), true, budget).total;
+    const size_t bare = sigma0_lds(N, J.t.W, (int)sizeof(T), true, 0).total;
+    int extra = 0;
+    hipError_t e;
+    if (bare <= budget) {
+        lds = std::max(lds, full <= budget ? full : bare);
+        extra = 1;
+    } else if ((e = launch_sigma0_packed(J, (int)sizeof(T), sp, stream)) != hipSuccess) {
+        return e;
+    }
+    int cus = 256, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 2)
+        cus = 256;
+    int groups = std::min((n + waves - 1) / waves, cus - extra);
+    if (g_max_workgroups.load() > 0) groups = std::min(groups, g_max_workgroups.load());
+    hipLaunchKernelGGL((k_packed<T, NB, V4, NBASE, ZOUT>), dim3(extra + groups), dim3(threads), lds, stream, J, sp, A,
+                       extra, (unsigned)lds);
+    return hipGetLastError();
+}
+
+template <typename T, int NB, bool V4>
+hipError_t launch_k(int k, const Job& J, const StageSpec& sp, const PackedStage<T>& A, hipStream_t stream) {
+    if (k == 0) return launch_t<T, NB, V4, 0, false>(J, sp, A, stream);
+    if (k == 1) return launch_t<T, NB, V4, 1, true>(J, sp, A, stream);
+    return launch_t<T, NB, V4, 1, false>(J, sp, A, stream);
+}
+
+template <typename T>
+hipError_t launch_nb(int k, const Job& J, const StageSpec& sp, const PackedStage<T>& A, hipStream_t stream) {
+    const bool v4 = J.t.N % 4 == 0;
+    switch ((J.t.N + 15) / 16) {
+        case 2: return v4 ? launch_k<T, 2, true>(k, J, sp, A, stream) : launch_k<T, 2, false>(k, J, sp, A, stream);
+        case 3: return v4 ? launch_k<T, 3, true>(k, J, sp, A, stream) : launch_k<T, 3, false>(k, J, sp, A, stream);
+        case 4:
+            // FP64 tiles of four wavefronts exceed a CU's LDS
+            if constexpr (sizeof(T) == 4)
+                return v4 ? launch_k<T, 4, true>(k, J, sp, A, stream) : launch_k<T, 4, false>(k, J, sp, A, stream);
+            return hipErrorInvalidValue;
+        default: return hipErrorInvalidValue;
+    }
+}
+
+template <typename T>
+hipError_t stage(int k, const Job& J, const PackedRun& R, const StageSpec& sp, hipStream_t stream) {
+    const int N = J.t.N;
+    // slot of the bulk arrays: y, Y2 and Y4, Y3 (Job::rest 0..3 the same)
+    T* y = static_cast<T*>(J.rest[0]);
+    T* a = static_cast<T*>(J.rest[1]);
+    T* b = static_cast<T*>(J.rest[2]);
+    T* z = static_cast<T*>(R.z);
+    PackedStage<T> A{};
+    A.in = k == 0 ? y : k == 2 ? b : a;
+    A.out = k == 1 ? b : k == 3 ? y : a;
+    A.base = k == 3 ? z : y;
+    A.z = z;
+    const size_t plane = (size_t)J.n_low * N * N;
+    T* m[2] = {static_cast<T*>(R.mirror[0]), static_cast<T*>(R.mirror[1])};
+    A.mr_in = m[k & 1];
+    A.mi_in = m[k & 1] + plane;
+    A.mr_out = m[1 - (k & 1)];
+    A.mi_out = m[1 - (k & 1)] + plane;
+    const T* side_in = static_cast<const T*>(R.side[k & 1]);
+    A.side_out = static_cast<T*>(R.side[1 - (k & 1)]);
+    // w_in and the 2/3 of Z sum to exactly 1
+    A.w_in = k == 0 ? (T)1 : k == 3 ? (T)1 - (T)(2.0 / 3.0) : (T)0;
+    A.h = (T)(sp.hmul * J.dt);
+    if (J.n_low > 0) {
+        static std::once_flag once;
+        static hipError_t err = hipSuccess;
+        if (full_lds(once, err, reinterpret_cast<const void*>(&k_packed_plus<T>)) != hipSuccess) return err;
+        hipLaunchKernelGGL((k_packed_plus<T>), dim3(J.n_low), dim3(256),
+                           2 * N * (N + 1) * sizeof(T) + J.t.W * (sizeof(T) + 8) + (N + 1) * 4, stream, J.t, J.n_low,
+                           A.in, A.mr_in, A.mi_in, side_in, A.out);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return launch_nb<T>(k, J, sp, A, stream);
+}
+
+template <typename T>
+hipError_t begin(const Job& J, const PackedRun& R, hipStream_t stream) {
+    const int N = J.t.N, n = J.t.n_ado - 1;
+    T* mr = static_cast<T*>(R.mirror[0]);
+    T* mi = mr + (size_t)J.n_low * N * N;
+    if (R.complex_rest)
+        hipLaunchKernelGGL((k_pack<T>), dim3(n), dim3(256), N * (N + 1) * sizeof(T), stream, J.t, R.complex_rest,
+                           static_cast<T*>(J.rest[0]), mr, mi, static_cast<T*>(R.side[0]), J.n_low);
+    else if (J.n_low > 0)
+        hipLaunchKernelGGL((k_mirror<T>), dim3(J.n_low), dim3(256), 0, stream, static_cast<const T*>(J.rest[0]), mr,
+                           mi, N);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// Single jobs over Hermitian ADOs with a real H and 17 <= N <= 64 whose
+// workspace holds the packed arrays.  Below 17 states a tile is mostly
+// padding and the neighbour rows, not the state, are the bytes.
+bool packed_plan(const Job& J, int precision, size_t sigma0_bytes, size_t work_bytes, size_t offset, PackedLayout* L) {
+    const Tables& t = J.t;
+    const int64_t n = t.n_ado - 1;
+    if (!J.herm || t.h_complex || t.N < 17 || t.N > (precision == 0 ? 48 : 64) || n < 1) return false;
+    const size_t ts = precision == 0 ? 8 : 4, NN = (size_t)t.N * t.N;
+    auto align256 = [](size_t x) { return (x + 255) & ~size_t(255); };
+    *L = PackedLayout{};
+    size_t o = offset;
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o += align256(std::max<size_t>(bytes, 1));
+        return at;
+    };
+    for (int k = 0; k < 3; ++k) L->sig0[k] = take(sigma0_bytes);
+    for (int k = 0; k < 3; ++k) L->array[k] = take((size_t)n * NN * ts);
+    for (int k = 0; k < 2; ++k) L->mirror[k] = take(2 * (size_t)J.n_low * NN * ts);
+    if (precision != 2) L->y = take((size_t)n * NN * ts);
+    if (o > work_bytes) return false;
+    // side rows where they fit too (a packed state leaves no room for them)
+    if (precision != 2 && J.n_low > 0 && (n - J.n_low) * t.D < (int64_t(1) << 31)) {
+        for (int k = 0; k < 2; ++k) L->side[k] = take(2 * (size_t)(n - J.n_low) * t.D * t.N * ts);
+        if (o > work_bytes) L->side[0] = L->side[1] = 0;
+    }
+    return true;
+}
+
+hipError_t packed_begin(const Job& J, const PackedRun& R, int precision, hipStream_t stream) {
+    return precision == 0 ? begin<double>(J, R, stream) : begin<float>(J, R, stream);
+}
+
+hipError_t packed_stage(int k, const Job& J, const PackedRun& R, int precision, const StageSpec& sp,
+                        hipStream_t stream) {
+    return precision == 0 ? stage<double>(k, J, R, sp, stream) : stage<float>(k, J, R, sp, stream);
+}
+
+hipError_t packed_end(const Job& J, const PackedRun& R, int precision, hipStream_t stream) {
+    if (!R.complex_rest) return hipSuccess;
+    const int N = J.t.N, n = J.t.n_ado - 1;
+    if (precision == 0)
+        hipLaunchKernelGGL((k_unpack<double>), dim3(n), dim3(256), N * (N + 1) * 8, stream,
+                           static_cast<const double*>(J.rest[0]), R.complex_rest, N);
+    else
+        hipLaunchKernelGGL((k_unpack<float>), dim3(n), dim3(256), N * (N + 1) * 4, stream,
+                           static_cast<const float*>(J.rest[0]), R.complex_rest, N);
+    return hipGetLastError();
+}
+
+}  // namespace heom
