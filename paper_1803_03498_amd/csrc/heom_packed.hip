@@ -1,5 +1,5 @@
-// Propagation of Hermitian ADOs in packed form (real H, 17 <= N <= 64,
-// HEOM_FP32_MIXED, HEOM_FP64 and HEOM_FP32_HERM): eq. HEOM of the section
+// Propagation of Hermitian ADOs in packed form (real H; HEOM_FP32_MIXED and
+// HEOM_FP32_HERM with 17 <= N <= 64, HEOM_FP64 with 10 <= N <= 48): eq. HEOM of the section
 // "HEOM formalism" of Kramer et al., arXiv:1803.03498, fused with RK4.
 //
 // A Hermitian matrix is half redundant, and these runs are bound by the bytes
@@ -49,6 +49,12 @@
 // reads of a top-level ADO is the row of each of its links; every stage leaves
 // those rows side by side ("side" rows), because a row of a Hermitian matrix
 // is half a row and half a column of P (48 sites: 0.43 ms per stage without).
+//
+// Up to 32 states a wavefront's work on one ADO is short, and the chain of
+// waits (links, then their rows, then the bases) bounds it: links, tile and
+// bases are read ahead, and only as many groups of links are taken as an ADO
+// has (14 sites, 237336 ADOs, FP64: 0.60 ms per stage without, 0.38 with; 24
+// sites, 20475 ADOs, FP32: 61 and 58 us).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -62,17 +68,29 @@
 namespace heom {
 namespace {
 
-template <typename T>
-struct Vec4;
+// PW elements of a P at element alignment (rows of odd N start anywhere)
+template <typename T, int PW>
+struct Vec;
 template <>
-struct Vec4<float> {
-    // element alignment: rows of odd N start anywhere
+struct Vec<float, 4> {
     typedef float type __attribute__((ext_vector_type(4), aligned(4)));
 };
 template <>
-struct Vec4<double> {
+struct Vec<double, 2> {
+    typedef double type __attribute__((ext_vector_type(2), aligned(8)));
+};
+template <>
+struct Vec<double, 4> {
     typedef double type __attribute__((ext_vector_type(4), aligned(8)));
 };
+// Elements of a lane's piece.  16 bytes: 32 bytes from lane to lane cost twice
+// the cache and LDS cycles (FP64, 14 sites: 0.382 against 0.406 ms per stage).
+// One wavefront per SIMD counts instructions instead (FP64, 48 sites: 2.35 ms
+// with four elements, 2.45 ms with two).
+template <typename T, int NB>
+constexpr int packed_piece() {
+    return sizeof(T) == 4 || NB == 3 ? 4 : 2;
+}
 
 template <typename T>
 struct PackedStage {
@@ -89,7 +107,7 @@ struct PackedStage {
 // Wavefronts per SIMD that registers and LDS allow; one workgroup per CU.
 template <typename T, int NB>
 constexpr int packed_waves() {
-    return sizeof(T) == 4 ? (NB == 2 ? 4 : NB == 3 ? 3 : 2) : (NB == 2 ? 2 : 1);
+    return sizeof(T) == 4 ? (NB == 2 ? 4 : NB == 3 ? 3 : 2) : (NB == 1 ? 4 : NB == 2 ? 2 : 1);
 }
 template <typename T, int NB>
 constexpr int packed_threads() {
@@ -109,7 +127,7 @@ constexpr size_t packed_lds() {
                         (size_t)(packed_threads<T, NB>() / 64) * 16 * NB * packed_stride<NB>());
 }
 
-template <typename T, int NB, bool V4, int NBASE, bool ZOUT>
+template <typename T, int NB, bool VA, int NBASE, bool ZOUT>
 __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
     amdgpu_waves_per_eu((packed_waves<T, NB>())))) void k_packed(Job J, StageSpec sp, PackedStage<T> A,
                                                                  int s0_blocks, unsigned lds_total) {
@@ -119,8 +137,10 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
         sigma0_stage<T, false, false, true>(J, nullptr, 0, sp, lds_total, smem);
         return;
     }
-    using V = typename Vec4<T>::type;
-    typedef T VL __attribute__((ext_vector_type(4)));  // aligned, in LDS
+    constexpr int PW = packed_piece<T, NB>();
+    using V = typename Vec<T, PW>::type;
+    typedef T VP __attribute__((ext_vector_type(PW)));  // aligned, in LDS
+    typedef T VL __attribute__((ext_vector_type(4)));
     using acc_t = typename mfma_acc<T>::type;
     constexpr int LS = packed_stride<NB>(), TILE = 16 * NB * LS, NT = NB * (NB + 1) / 2;
     const Tables& t = J.t;
@@ -152,16 +172,16 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
     const int stride = ((int)gridDim.x - s0_blocks) * waves;
     int lane = threadIdx.x & 63;
 
-    // linear pieces of P: four elements at 4 (lane + 64 q), q < nq; beyond the
-    // end the last four once more (the same values from several lanes; the
+    // linear pieces of P: PW elements at PW (lane + 64 q), q < nq; beyond the
+    // end the last ones once more (the same values from several lanes; the
     // loads are not conditional on q, which would keep undefined values live)
-    constexpr int Q = NB * NB;
-    int nq = (NN + 255) / 256;
+    constexpr int Q = NB * NB * 4 / PW;
+    int nq = (NN + 64 * PW - 1) / (64 * PW);
     const uint32_t by_n = 0xFFFFFFFFu / (uint32_t)N + 1u;  // e / N = mulhi(e, by_n) for e < 2^16
     struct Pieces {
         V v[Q];
     };
-    auto first_of = [&](int q) { return min(4 * (lane + 64 * q), NN - 4); };
+    auto first_of = [&](int q) { return min(PW * (lane + 64 * q), NN - PW); };
     auto load = [&](const T* src, Pieces& p) {
 #pragma unroll
         for (int q = 0; q < Q; ++q)
@@ -172,34 +192,33 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
         *reinterpret_cast<gptr<V>>(G(reinterpret_cast<char*>(dst)) + (uint32_t)first_of(q) * (uint32_t)sizeof(T)) = v;
     };
     auto lds_at = [&](int e) { return S + (int)__umulhi((uint32_t)e, by_n) * (LS - N) + e; };
-    // four elements from e on: those within `left` in e's row, the rest in the
-    // next (N >= 17, so no more rows)
+    // PW elements from e on: those within `left` in e's row, the rest in the next
     auto lds_row = [&](int e, T*& at, int& left) {
         const int i = (int)__umulhi((uint32_t)e, by_n);
         at = S + i * (LS - N) + e;
         left = N - (e - i * N);
     };
     auto piece_to_lds = [&](int q, V v) {
-        if constexpr (V4) {
-            *reinterpret_cast<VL*>(lds_at(first_of(q))) = v;
+        if constexpr (VA) {
+            *reinterpret_cast<VP*>(lds_at(first_of(q))) = v;
         } else {
             T* at;
             int left;
             lds_row(first_of(q), at, left);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) at[r < left ? r : r + LS - N] = v[r];
+            for (int r = 0; r < PW; ++r) at[r < left ? r : r + LS - N] = v[r];
         }
     };
     auto piece_from_lds = [&](int q) -> V {
         V v;
-        if constexpr (V4) {
-            v = *reinterpret_cast<const VL*>(lds_at(first_of(q)));
+        if constexpr (VA) {
+            v = *reinterpret_cast<const VP*>(lds_at(first_of(q)));
         } else {
             T* at;
             int left;
             lds_row(first_of(q), at, left);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = at[r < left ? r : r + LS - N];
+            for (int r = 0; r < PW; ++r) v[r] = at[r < left ? r : r + LS - N];
         }
         return v;
     };
@@ -209,49 +228,70 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
         __builtin_amdgcn_wave_barrier();
     };
 
-    // "-" links 4q + g of ADO u: weighted row, columns 16 jb + jl
-    auto link = [&](int u, int q, int& s, T xr[NB], T xi[NB]) {
-        const int c = lane & 15, g = lane >> 4, jl = sizeof(T) == 8 ? 4 * (c & 3) + (c >> 2) : c;
-        const int a = 4 * q + g;
-        const size_t at = (size_t)u * Dm + min(a, Dm - 1);
-        const int nb = a < Dm ? G(reinterpret_cast<const pair_i*>(t.mlist))[at].x : -1;
-        s = nb >= 0 ? G(t.mlist_site)[at] : -1;
+    // the "-" links of an ADO, one per lane, read one ADO ahead, so that
+    // rows and tile are a single wait apart
+    struct Links {
+        int nb, s;
         T ml, mc;
+    };
+    auto links = [&](int u) {
+        Links l;
+        const size_t at = (size_t)u * Dm + min(lane, Dm - 1);
+        l.nb = G(reinterpret_cast<const pair_i*>(t.mlist))[at].x;
+        l.s = G(t.mlist_site)[at];
         if constexpr (sizeof(T) == 4) {
             const pair_f w = G(reinterpret_cast<const pair_f*>(t.mlist_w32))[at];
-            ml = w.x;
-            mc = w.y;
+            l.ml = w.x;
+            l.mc = w.y;
         } else {
             const pair_d w = G(reinterpret_cast<const pair_d*>(t.mlist_w))[at];
-            ml = w.x;
-            mc = w.y;
+            l.ml = w.x;
+            l.mc = w.y;
         }
+        return l;
+    };
+    // links 4q + g: their rows, columns 16 jb + jl
+    struct Rows {
+        int s;
+        T ml, mc, re[NB], im[NB];
+    };
+    auto rows = [&](const Links& l, int count, int q) {
+        const int c = lane & 15, g = lane >> 4, jl = sizeof(T) == 8 ? 4 * (c & 3) + (c >> 2) : c;
+        const int a = 4 * q + g;
+        Rows R;
+        // every lane takes part: a lane left out would read as 0
+        int nb = __shfl(l.nb, a);
+        R.s = __shfl(l.s, a);
+        R.ml = __shfl(l.ml, a);
+        R.mc = __shfl(l.mc, a);
+        if (a >= count) nb = -1;
+        if (nb < 0) R.s = -1;
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb) {
             const int col = min(16 * jb + jl, N - 1);
-            T re = 0, im = 0;
+            R.re[jb] = R.im[jb] = (T)0;
             if (nb > 0) {
-                const size_t o = (size_t)(nb - 1) * NN + s * N + col;
-                re = G(A.mr_in)[o];
-                im = G(A.mi_in)[o];
+                const size_t o = (size_t)(nb - 1) * NN + R.s * N + col;
+                R.re[jb] = G(A.mr_in)[o];
+                R.im[jb] = G(A.mi_in)[o];
             } else if (nb == 0) {
-                const cpx<double> v = ld<double>(J.sig0[sp.in], (size_t)s * N + col);
-                re = (T)v.re;
-                im = (T)v.im;
+                const cpx<double> v = ld<double>(J.sig0[sp.in], (size_t)R.s * N + col);
+                R.re[jb] = (T)v.re;
+                R.im[jb] = (T)v.im;
             }
-            // (ml + i mc) x, the V^o part alone on the diagonal
-            const T m = 16 * jb + jl == s ? (T)0 : mc;
-            xr[jb] = nb >= 0 ? ml * re - m * im : (T)0;
-            xi[jb] = nb >= 0 ? ml * im + m * re : (T)0;
         }
+        return R;
     };
 
     // The next tile and this one's stage base are read ahead where the
     // registers allow; at 32 < N in FP32 three wavefronts per SIMD cover the
     // waits instead (the base then goes out before the elementwise part).
-    constexpr bool kAhead = sizeof(T) == 8 || NB == 2;
+    constexpr bool kAhead = sizeof(T) == 8 || NB <= 2;
+    // one tile row: also this tile itself and the next four links' rows
+    constexpr bool kRoom = NB == 1;
     Pieces pre;
     if constexpr (kAhead) load(A.in + (size_t)(min(first, t.n_ado - 1) - 1) * NN, pre);
+    Links ahead = links(min(first, t.n_ado - 1));
     for (int u = first; u < t.n_ado; u += stride) {
         // through an empty asm: addresses and conditions hoisted out of the
         // loop would hold (and spill) a register each
@@ -260,23 +300,27 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
         // column (and operand row) of this lane inside a tile
         const int jl = sizeof(T) == 8 ? 4 * (c & 3) + (c >> 2) : c;
         const size_t tile = (size_t)(u - 1) * NN;
-        int s0;
-        T xr[NB], xi[NB];
-        Pieces bas;
+        Pieces bas, p;
+        const T gam = (T)G(t.damping)[u];
+        const Links own_links = ahead;
+        // the active links come first
+        const int count = __popcll(__ballot(lane < Dm && own_links.s >= 0));
+        Rows ra, rb;
         {
-            Pieces p;
             if constexpr (kAhead) p = pre;
             else load(A.in + tile, p);
-            link(u, 0, s0, xr, xi);
+            ra = rows(own_links, count, 0);
+            if constexpr (kRoom) rb = rows(own_links, count, 1);
             if constexpr (kAhead) {
                 if constexpr (NBASE > 0) load(A.base + tile, bas);
                 load(A.in + (size_t)(min(u + stride, t.n_ado - 1) - 1) * NN, pre);
             }
+            if constexpr (kRoom) ahead = links(min(u + stride, t.n_ado - 1));
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
                 if (q < nq) piece_to_lds(q, p.v[q]);
-                if (!V4) __builtin_amdgcn_sched_barrier(0);  // four addresses per piece
+                if (!VA) __builtin_amdgcn_sched_barrier(0);  // four addresses per piece
             }
         }
         fence();
@@ -337,9 +381,16 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
         }
         // E R + (E R)^dagger, four links at a time
         for (int q = 0;;) {
-            T E[NB];
+            T E[NB], xr[NB], xi[NB];
 #pragma unroll
-            for (int jb = 0; jb < NB; ++jb) E[jb] = s0 == 16 * jb + jl ? (T)1 : (T)0;
+            for (int jb = 0; jb < NB; ++jb) {
+                const bool at = 16 * jb + jl == ra.s;
+                E[jb] = at ? (T)1 : (T)0;
+                // (ml + i mc) x, the V^o part alone on the diagonal
+                const T m = at ? (T)0 : ra.mc;
+                xr[jb] = ra.ml * ra.re[jb] - m * ra.im[jb];
+                xi[jb] = ra.ml * ra.im[jb] + m * ra.re[jb];
+            }
 #pragma unroll
             for (int a = 0; a < NB; ++a)
 #pragma unroll
@@ -350,13 +401,21 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
                     re[x] = mfma16(xr[a], E[b], re[x]);
                     im[x] = mfma16(-xi[b], E[a], im[x]);
                 }
-            if (4 * ++q >= Dm) break;
-            link(u, q, s0, xr, xi);
+            if (4 * ++q >= count) break;
+            if constexpr (kRoom) {
+                ra = rb;
+                rb = rows(own_links, count, q + 1);
+            } else {
+                ra = rows(own_links, count, q);
+            }
         }
         const bool low = u <= J.n_low;
+        Pieces plus;
+        if constexpr (kRoom)
+            if (low) load(A.out + tile, plus);
+        if constexpr (!kRoom) ahead = links(min(u + stride, t.n_ado - 1));
         if constexpr (!kAhead && NBASE > 0) load(A.base + tile, bas);
         // w_in sigma + h (f - damping) at [j][i], in place of sigma
-        const T gam = (T)G(t.damping)[u];
         fence();
 #pragma unroll
         for (int rb = 0; rb < NB; ++rb)
@@ -381,8 +440,17 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
                     }
                     o[r] = A.w_in * s[r] + A.h * (f - gm * s[r]);
                 }
-                if (V4 || cb < NB - 1) {
-                    if (j < N && i0 < N) *reinterpret_cast<VL*>(at) = o;
+                if (cb < NB - 1) {
+                    if (j < N) *reinterpret_cast<VL*>(at) = o;
+                } else if (VA) {
+#pragma unroll
+                    for (int r = 0; r < 4; r += PW)
+                        if (j < N && i0 + r < N) {
+                            VP part;
+#pragma unroll
+                            for (int k = 0; k < PW; ++k) part[k] = o[r + k];
+                            *reinterpret_cast<VP*>(at + r) = part;
+                        }
                 } else {
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
@@ -392,47 +460,47 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
         fence();
         // linear again: the bases, and what the next stages need
         __builtin_amdgcn_sched_barrier(0);
-        Pieces own;
-        if constexpr (ZOUT) load(A.in + tile, own);
+        if constexpr (ZOUT && !kRoom) load(A.in + tile, p);
         const bool again = low || A.side_out;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             if (q >= nq) continue;
             V o = piece_from_lds(q);
-            if (low)
-                o += A.h * *reinterpret_cast<gcptr<V>>(G(reinterpret_cast<const char*>(A.out + tile)) +
-                                                       (uint32_t)first_of(q) * (uint32_t)sizeof(T));
+            if (low) {
+                if constexpr (!kRoom)
+                    plus.v[q] = *reinterpret_cast<gcptr<V>>(G(reinterpret_cast<const char*>(A.out + tile)) +
+                                                            (uint32_t)first_of(q) * (uint32_t)sizeof(T));
+                o += A.h * plus.v[q];
+            }
             if constexpr (NBASE > 0) o += bas.v[q];
             store_piece(A.out + tile, q, o);
             // (-y + Y2 + 2 Y3)/3 by increments on 2/3 y
             if constexpr (ZOUT)
                 store_piece(A.z + tile, q,
                             (T)(2.0 / 3.0) * bas.v[q] +
-                                (T)(1.0 / 3.0) * ((own.v[q] - bas.v[q]) + (T)2 * (o - bas.v[q])));
+                                (T)(1.0 / 3.0) * ((p.v[q] - bas.v[q]) + (T)2 * (o - bas.v[q])));
             if (again) piece_to_lds(q, o);
-            if (!V4) __builtin_amdgcn_sched_barrier(0);
+            if (!VA) __builtin_amdgcn_sched_barrier(0);
         }
         if (again) {
             fence();
             if (low) {
                 // full planes for the next stage's "-" rows
                 for (int e = lane; e < NN; e += 64) {
-                    const int i = e / N, j = e - i * N;
+                    const int i = (int)__umulhi((uint32_t)e, by_n), j = e - i * N;
                     const T up = S[min(i, j) * LS + max(i, j)], lo = S[max(i, j) * LS + min(i, j)];
                     G(A.mr_out)[tile + e] = up;
                     G(A.mi_out)[tile + e] = i < j ? lo : (i > j ? -lo : (T)0);
                 }
             } else {
                 // the rows that lower levels read of this ADO
-                for (int a = 0; a < Dm; ++a) {
-                    const size_t at = (size_t)u * Dm + a;
-                    const int s = uniform(G(t.mlist_site)[at]);
-                    if (s < 0) break;
-                    if (lane < N) {
-                        const T up = S[min(s, lane) * LS + max(s, lane)], lo = S[max(s, lane) * LS + min(s, lane)];
-                        st<T>(A.side_out, ((size_t)(u - 1 - J.n_low) * Dm + a) * N + lane,
-                              cpx<T>{up, s < lane ? lo : (s > lane ? -lo : (T)0)});
-                    }
+                for (int x0 = 0; x0 < count * N; x0 += 64) {
+                    const int x = x0 + lane, a = (int)__umulhi((uint32_t)x, by_n), j = x - a * N;
+                    const int s = __shfl(own_links.s, a);  // by every lane
+                    if (x >= count * N) continue;
+                    const T up = S[min(s, j) * LS + max(s, j)], lo = S[max(s, j) * LS + min(s, j)];
+                    st<T>(A.side_out, (size_t)(u - 1 - J.n_low) * Dm * N + x,
+                          cpx<T>{up, s < j ? lo : (s > j ? -lo : (T)0)});
                 }
             }
             fence();
@@ -581,9 +649,9 @@ hipError_t full_lds(std::once_flag& once, hipError_t& err, const void* fn) {
     return err;
 }
 
-template <typename T, int NB, bool V4, int NBASE, bool ZOUT>
+template <typename T, int NB, bool VA, int NBASE, bool ZOUT>
 hipError_t launch_t(const Job& J, const StageSpec& sp, const PackedStage<T>& A, hipStream_t stream) {
-    const void* fn = reinterpret_cast<const void*>(&k_packed<T, NB, V4, NBASE, ZOUT>);
+    const void* fn = reinterpret_cast<const void*>(&k_packed<T, NB, VA, NBASE, ZOUT>);
     static std::once_flag once;
     static hipError_t err = hipSuccess;
     if (full_lds(once, err, fn) != hipSuccess) return err;
@@ -609,28 +677,32 @@ hipError_t launch_t(const Job& J, const StageSpec& sp, const PackedStage<T>& A, 
         cus = 256;
     int groups = std::min((n + waves - 1) / waves, cus - extra);
     if (g_max_workgroups.load() > 0) groups = std::min(groups, g_max_workgroups.load());
-    hipLaunchKernelGGL((k_packed<T, NB, V4, NBASE, ZOUT>), dim3(extra + groups), dim3(threads), lds, stream, J, sp, A,
+    hipLaunchKernelGGL((k_packed<T, NB, VA, NBASE, ZOUT>), dim3(extra + groups), dim3(threads), lds, stream, J, sp, A,
                        extra, (unsigned)lds);
     return hipGetLastError();
 }
 
-template <typename T, int NB, bool V4>
+template <typename T, int NB, bool VA>
 hipError_t launch_k(int k, const Job& J, const StageSpec& sp, const PackedStage<T>& A, hipStream_t stream) {
-    if (k == 0) return launch_t<T, NB, V4, 0, false>(J, sp, A, stream);
-    if (k == 1) return launch_t<T, NB, V4, 1, true>(J, sp, A, stream);
-    return launch_t<T, NB, V4, 1, false>(J, sp, A, stream);
+    if (k == 0) return launch_t<T, NB, VA, 0, false>(J, sp, A, stream);
+    if (k == 1) return launch_t<T, NB, VA, 1, true>(J, sp, A, stream);
+    return launch_t<T, NB, VA, 1, false>(J, sp, A, stream);
 }
 
 template <typename T>
 hipError_t launch_nb(int k, const Job& J, const StageSpec& sp, const PackedStage<T>& A, hipStream_t stream) {
-    const bool v4 = J.t.N % 4 == 0;
+    const bool va = J.t.N % (sizeof(T) == 4 || J.t.N > 32 ? 4 : 2) == 0;
     switch ((J.t.N + 15) / 16) {
-        case 2: return v4 ? launch_k<T, 2, true>(k, J, sp, A, stream) : launch_k<T, 2, false>(k, J, sp, A, stream);
-        case 3: return v4 ? launch_k<T, 3, true>(k, J, sp, A, stream) : launch_k<T, 3, false>(k, J, sp, A, stream);
+        case 1:
+            if constexpr (sizeof(T) == 8)
+                return va ? launch_k<T, 1, true>(k, J, sp, A, stream) : launch_k<T, 1, false>(k, J, sp, A, stream);
+            return hipErrorInvalidValue;
+        case 2: return va ? launch_k<T, 2, true>(k, J, sp, A, stream) : launch_k<T, 2, false>(k, J, sp, A, stream);
+        case 3: return va ? launch_k<T, 3, true>(k, J, sp, A, stream) : launch_k<T, 3, false>(k, J, sp, A, stream);
         case 4:
             // FP64 tiles of four wavefronts exceed a CU's LDS
             if constexpr (sizeof(T) == 4)
-                return v4 ? launch_k<T, 4, true>(k, J, sp, A, stream) : launch_k<T, 4, false>(k, J, sp, A, stream);
+                return va ? launch_k<T, 4, true>(k, J, sp, A, stream) : launch_k<T, 4, false>(k, J, sp, A, stream);
             return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
@@ -689,13 +761,18 @@ hipError_t begin(const Job& J, const PackedRun& R, hipStream_t stream) {
 
 }  // namespace
 
-// Single jobs over Hermitian ADOs with a real H and 17 <= N <= 64 whose
-// workspace holds the packed arrays.  Below 17 states a tile is mostly
-// padding and the neighbour rows, not the state, are the bytes.
+// Single jobs over Hermitian ADOs with a real H whose workspace holds the
+// packed arrays.  Small matrices pay for padding and for side rows, which do
+// not halve: in FP64 10 states still gain (53130 ADOs: 0.38 ms per step against
+// 0.41 with the complex kernels; 14 states, 237336 ADOs: 2.1 against 3.2), in
+// FP32 up to 16 they do not (16 states, 74613 ADOs: 0.52 against 0.52; 10
+// states, 230230 ADOs: 1.22 against 1.11).  A wavefront holds the links of an
+// ADO, so at most 64 of them.
 bool packed_plan(const Job& J, int precision, size_t sigma0_bytes, size_t work_bytes, size_t offset, PackedLayout* L) {
     const Tables& t = J.t;
     const int64_t n = t.n_ado - 1;
-    if (!J.herm || t.h_complex || t.N < 17 || t.N > (precision == 0 ? 48 : 64) || n < 1) return false;
+    if (!J.herm || t.h_complex || t.N < (precision == 0 ? 10 : 17) || t.N > (precision == 0 ? 48 : 64) || n < 1 || t.D > 64)
+        return false;
     const size_t ts = precision == 0 ? 8 : 4, NN = (size_t)t.N * t.N;
     auto align256 = [](size_t x) { return (x + 255) & ~size_t(255); };
     *L = PackedLayout{};
