@@ -1008,6 +1008,7 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
         }
         j.rest[3] = j.rest[1];
         pack.z = w + lay.array[2];
+        if (lay.h) pack.h = w + lay.h;
         if (lay.y) {
             pack.complex_rest = io.rest;
             j.rest[0] = w + lay.y;

@@ -152,11 +152,13 @@ struct PackedLayout {             // offsets into the propagation workspace
     size_t sig0[3], array[3], mirror[2];
     size_t y;                     // packed copy of a complex state (0: the state is packed)
     size_t side[2];               // 0: no room
+    size_t h;                     // H in operand order (0: kept in LDS)
 };
 struct PackedRun {
     void* z;                      // (-y + Y2 + 2 Y3)/3
     void* mirror[2];              // planes of the ADOs 1..n_low, of stage inputs in turn
     void* side[2];                // coupling rows of the top level, of stage inputs in turn, or null
+    void* h;                      // H in operand order, or null
     void* complex_rest;           // the caller's complex ADOs, null if packed
 };
 bool packed_plan(const Job& j, int precision, size_t sigma0_bytes, size_t work_bytes, size_t offset,

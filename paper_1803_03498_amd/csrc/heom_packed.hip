@@ -15,18 +15,15 @@
 //   4: y' = Y4/3 + Z + dt/6 f(Y4)                            read 2, write 1
 //
 // One wavefront computes one ADO, with no barrier anywhere.  With sigma = A + iB
-// (A symmetric, B antisymmetric)
-//   Re(-i[H, sigma]) = H B - B H,    Im(-i[H, sigma]) = -(H A - A H),
-// and only half of each is needed: 16 x 16 tiles (I, J) with I >= J of the
-// real part, I <= J of the imaginary one.  A tile
-//   T_IJ = sum_K +-H_IK X_KJ -+ X_IK H_KJ
-// is two matrix-core products per K and k-step.  X_IK as the A operand has
-// the registers of X_KI as the B operand (X^T = +-X, and H is symmetric), so
-// the tiles (K, J), all J, serve both, and nothing is transposed through
-// memory between product and result.  That is 4/3 of the multiplications of
-// H sigma alone; in return there is no second pair of LDS planes and no
-// barrier, whose latency held the complex kernel at 1.5 ms per stage at 48
-// sites however few bytes the stage moved.
+// (A symmetric, B antisymmetric) and U = H B, V = -H A
+//   Re(-i[H, sigma]) = U + U^T,    Im(-i[H, sigma]) = V - V^T,
+// 2 N^3 real multiplications per plane and no more.  U[i][j] is added where
+// the lane's four rows i are contiguous (P[j][i]), then U[j][i] in place with
+// the roles swapped, through the wavefront's LDS tile.  (Without that exchange,
+// computing half the 16 x 16 tiles of H B - B H with operands taken from either
+// side costs 4/3 as many products, and 48 sites took 1.05 to 1.35 ms per stage
+// in FP32 and 2.35 to 2.81 in FP64, against 0.92 to 1.33 and 1.97 to 2.74; 24
+// sites 57 to 63 us against 52 to 58.)
 //
 // Global accesses are linear (P as it lies in memory, 16 bytes per lane): the
 // tile goes to this wavefront's own LDS tile, operands and results use that.
@@ -40,8 +37,14 @@
 // permuted by the same map.)  The tile's stride 16 NB + 4 keeps both accesses
 // free of bank conflicts and makes every offset a constant.
 //
+// H lies in LDS in operand order, one 16-byte access per block.  FP64 above 32
+// states has no room for it next to the tiles of two wavefronts per SIMD, which
+// cover each other's waits (one per SIMD: 2.35 ms): it reads the same table
+// from memory (L1 and L2; from H itself, rows apart, 2.6 ms).
+//
 // "-" links ride along as one more product per four links: with E[i][a] =
-// (i == s_a) and the weighted rows R_a, E R + (E R)^dagger.  The rows of the
+// (i == s_a) and the weighted rows R_a, E R + (E R)^dagger: E Re R joins U and
+// E Im R joins V.  The rows of the
 // lower-level neighbours come from mirrors: real and imaginary planes, full
 // N x N, of the ADOs below the top level (a few percent), written by every
 // stage.  "+" links exist below the top level only; k_packed_plus sums them
@@ -60,6 +63,7 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "heom_device.h"
 #include "heom_internal.h"
@@ -68,29 +72,19 @@
 namespace heom {
 namespace {
 
-// PW elements of a P at element alignment (rows of odd N start anywhere)
-template <typename T, int PW>
-struct Vec;
+// A lane's piece of a P, at element alignment (rows of odd N start anywhere):
+// 16 bytes.  32 bytes from lane to lane cost twice the cache and LDS cycles
+// (FP64, 14 sites: 0.406 against 0.382 ms per stage).
+template <typename T>
+struct Vec16;
 template <>
-struct Vec<float, 4> {
+struct Vec16<float> {
     typedef float type __attribute__((ext_vector_type(4), aligned(4)));
 };
 template <>
-struct Vec<double, 2> {
+struct Vec16<double> {
     typedef double type __attribute__((ext_vector_type(2), aligned(8)));
 };
-template <>
-struct Vec<double, 4> {
-    typedef double type __attribute__((ext_vector_type(4), aligned(8)));
-};
-// Elements of a lane's piece.  16 bytes: 32 bytes from lane to lane cost twice
-// the cache and LDS cycles (FP64, 14 sites: 0.382 against 0.406 ms per stage).
-// One wavefront per SIMD counts instructions instead (FP64, 48 sites: 2.35 ms
-// with four elements, 2.45 ms with two).
-template <typename T, int NB>
-constexpr int packed_piece() {
-    return sizeof(T) == 4 || NB == 3 ? 4 : 2;
-}
 
 template <typename T>
 struct PackedStage {
@@ -101,13 +95,15 @@ struct PackedStage {
     const T *mr_in, *mi_in;  // mirror planes of `in`, [n_low][N][N]
     T *mr_out, *mi_out;      // of `out`
     T* side_out;             // side rows of `out`, complex [top ADO][D][N], or null
+    const T* hop;            // H in operand order where LDS has no room for it
     T w_in, h;
 };
 
 // Wavefronts per SIMD that registers and LDS allow; one workgroup per CU.
+// One row block is FP64 only.
 template <typename T, int NB>
 constexpr int packed_waves() {
-    return sizeof(T) == 4 ? (NB == 2 ? 4 : NB == 3 ? 3 : 2) : (NB == 1 ? 4 : NB == 2 ? 2 : 1);
+    return sizeof(T) == 4 ? (NB == 2 ? 4 : NB == 3 ? 3 : 2) : (NB == 1 ? 4 : 2);
 }
 template <typename T, int NB>
 constexpr int packed_threads() {
@@ -116,15 +112,40 @@ constexpr int packed_threads() {
 // k-steps of the last K block of `rem` columns (1..16): lane group g takes the
 // columns kr g + r, r < kr, so that 8 columns need 2 products, not 4.
 __host__ __device__ constexpr int packed_last_steps(int rem) { return (rem + 3) / 4; }
-template <int NB>
+template <typename T, int NB>
+constexpr bool packed_h_in_lds() {
+    return sizeof(T) == 4 || NB < 3;
+}
+template <typename T, int NB>
 constexpr int packed_stride() {
-    return 16 * NB + 4;
+    return 16 * NB + (packed_h_in_lds<T, NB>() ? 4 : 2);
 }
 // LDS elements: H in operand order, Delta, one tile per wavefront
 template <typename T, int NB>
 constexpr size_t packed_lds() {
-    return sizeof(T) * (NB * NB * 256 + 16 * NB +
-                        (size_t)(packed_threads<T, NB>() / 64) * 16 * NB * packed_stride<NB>());
+    return sizeof(T) * ((packed_h_in_lds<T, NB>() ? NB * NB * 256 : 0) + 16 * NB +
+                        (size_t)(packed_threads<T, NB>() / 64) * 16 * NB * packed_stride<T, NB>());
+}
+
+// H as the A operand of block ik = I NB + K: lane (g, c) holds H[16I + jl][k],
+// k = 16K + steps g + r; zero outside N x N, which meets whatever the tile's
+// padding holds.
+template <typename T>
+__device__ __forceinline__ T h_operand(const Tables& t, int NB, int ik, int lane, int r) {
+    const int N = t.N, I = ik / NB, K = ik - I * NB;
+    const int c = lane & 15, g = lane >> 4, jl = sizeof(T) == 8 ? 4 * (c & 3) + (c >> 2) : c;
+    const int steps = K < NB - 1 ? 4 : packed_last_steps(N - 16 * (NB - 1));
+    const int row = 16 * I + jl, col = 16 * K + steps * g + r;
+    if (r >= steps || row >= N || col >= N) return (T)0;
+    if constexpr (sizeof(T) == 4) return G(t.h_re_f32)[row * N + col];
+    else return G(t.h_re)[row * N + col];
+}
+
+// The same in memory, [block][r / 2][lane][2].
+__global__ __launch_bounds__(256) void k_h_operand(Tables t, int NB, double* out) {
+    const int x = blockIdx.x * 256 + threadIdx.x;
+    if (x >= NB * NB * 256) return;
+    G(out)[x] = h_operand<double>(t, NB, x >> 8, (x >> 1) & 63, 2 * ((x >> 7) & 1) + (x & 1));
 }
 
 template <typename T, int NB, bool VA, int NBASE, bool ZOUT>
@@ -137,29 +158,21 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
         sigma0_stage<T, false, false, true>(J, nullptr, 0, sp, lds_total, smem);
         return;
     }
-    constexpr int PW = packed_piece<T, NB>();
-    using V = typename Vec<T, PW>::type;
+    constexpr int PW = 16 / sizeof(T);
+    using V = typename Vec16<T>::type;
     typedef T VP __attribute__((ext_vector_type(PW)));  // aligned, in LDS
     typedef T VL __attribute__((ext_vector_type(4)));
     using acc_t = typename mfma_acc<T>::type;
-    constexpr int LS = packed_stride<NB>(), TILE = 16 * NB * LS, NT = NB * (NB + 1) / 2;
+    constexpr int LS = packed_stride<T, NB>(), TILE = 16 * NB * LS;
+    constexpr bool kHlds = packed_h_in_lds<T, NB>();
     const Tables& t = J.t;
     const int N = t.N, NN = N * N, Dm = t.D > 0 ? t.D : 1;
     T* sH = reinterpret_cast<T*>(smem);
-    T* sDelta = sH + NB * NB * 256;
+    T* sDelta = sH + (kHlds ? NB * NB * 256 : 0);
     T* tiles = sDelta + 16 * NB;
-    for (int x = threadIdx.x; x < NB * NB * 256; x += blockDim.x) {
-        const int r = x & 3, ln = (x >> 2) & 63, ik = x >> 8, I = ik / NB, K = ik - I * NB;
-        const int c = ln & 15, g = ln >> 4, jl = sizeof(T) == 8 ? 4 * (c & 3) + (c >> 2) : c;
-        const int steps = K < NB - 1 ? 4 : packed_last_steps(N - 16 * (NB - 1));
-        const int row = 16 * I + jl, col = 16 * K + steps * g + r;
-        T v = (T)0;  // outside N x N: what the tile holds there meets these zeros
-        if (r < steps && row < N && col < N) {
-            if constexpr (sizeof(T) == 4) v = G(t.h_re_f32)[row * N + col];
-            else v = G(t.h_re)[row * N + col];
-        }
-        sH[x] = v;
-    }
+    if constexpr (kHlds)
+        for (int x = threadIdx.x; x < NB * NB * 256; x += blockDim.x)
+            sH[x] = h_operand<T>(t, NB, x >> 8, (x >> 2) & 63, x & 3);
     for (int x = threadIdx.x; x < 16 * NB; x += blockDim.x) sDelta[x] = x < N ? (T)G(t.delta_state)[x] : (T)0;
     // the padding of a tile stays zero
     for (int x = threadIdx.x; x < (int)(blockDim.x / 64) * TILE; x += blockDim.x) tiles[x] = (T)0;
@@ -284,9 +297,10 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
     };
 
     // The next tile and this one's stage base are read ahead where the
-    // registers allow; at 32 < N in FP32 three wavefronts per SIMD cover the
-    // waits instead (the base then goes out before the elementwise part).
-    constexpr bool kAhead = sizeof(T) == 8 || NB <= 2;
+    // registers allow; above 32 states the wavefronts of a SIMD (three in
+    // FP32, two in FP64) cover the waits instead, and the bases are read when
+    // the accumulators are done with.
+    constexpr bool kAhead = NB <= 2;
     // one tile row: also this tile itself and the next four links' rows
     constexpr bool kRoom = NB == 1;
     Pieces pre;
@@ -309,7 +323,7 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
         {
             if constexpr (kAhead) p = pre;
             else load(A.in + tile, p);
-            ra = rows(own_links, count, 0);
+            if constexpr (kHlds) ra = rows(own_links, count, 0);
             if constexpr (kRoom) rb = rows(own_links, count, 1);
             if constexpr (kAhead) {
                 if constexpr (NBASE > 0) load(A.base + tile, bas);
@@ -324,62 +338,75 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
             }
         }
         fence();
-        acc_t re[NT], im[NT];  // tiles (a, b) of the real part, (b, a) of the imaginary one, a >= b
+        // U = H B + E R_re and V = -H A + E R_im: the real part is U + U^T, the
+        // imaginary one V - V^T
+        acc_t accU[NB * NB], accV[NB * NB];
 #pragma unroll
-        for (int x = 0; x < NT; ++x) re[x] = im[x] = acc_t{0, 0, 0, 0};
+        for (int x = 0; x < NB * NB; ++x) accU[x] = accV[x] = acc_t{0, 0, 0, 0};
+        auto product = [&](auto imag, acc_t(&W)[NB * NB]) {
 #pragma unroll
-        for (int K = 0; K < NB; ++K) {
-            // the scheduler would otherwise load every K block's operands first
-            __builtin_amdgcn_sched_barrier(0);
-            const int steps = K < NB - 1 ? 4 : kr, k0 = steps * g;
-            const T* Sd = S + k0 * LS + jl;  // direct: [k0 + r][jl]
-            const T* St = S + jl * LS + k0;  // transposed: [jl][k0 + r]
-            T XA[NB][4], XB[NB][4], HR[NB][4];
+            for (int K = 0; K < NB; ++K) {
+                // the scheduler would otherwise load every K block's operands first
+                __builtin_amdgcn_sched_barrier(0);
+                const int steps = K < NB - 1 ? 4 : kr, k0 = steps * g;
+                const T* Sd = S + (16 * K + k0) * LS + jl;  // direct: [k][jl]
+                const T* St = S + jl * LS + 16 * K + k0;    // transposed: [jl][k]
+                T X[NB][4], HR[NB][4];
 #pragma unroll
-            for (int jb = 0; jb < NB; ++jb) {
-                const VL hv = *reinterpret_cast<const VL*>(sH + ((jb * NB + K) * 64 + lane) * 4);
-                T tr[4];
-                if (K < NB - 1) {
-                    const VL v = *reinterpret_cast<const VL*>(St + 16 * jb * LS + 16 * K);
+                for (int jb = 0; jb < NB; ++jb) {
+                    if constexpr (kHlds) {
+                        const VL hv = *reinterpret_cast<const VL*>(sH + ((jb * NB + K) * 64 + lane) * 4);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) tr[r] = v[r];
-                } else {
+                        for (int r = 0; r < 4; ++r) HR[jb][r] = hv[r];
+                    } else {
+                        // [block][r / PW][lane][PW]: 16 bytes from lane to lane
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) tr[r] = St[16 * jb * LS + 16 * K + r];
+                        for (int r = 0; r < 4; r += PW) {
+                            const V hv = *reinterpret_cast<gcptr<V>>(
+                                G(A.hop) + (uint32_t)(((jb * NB + K) * 4 + r) * 64 + lane * PW));
+#pragma unroll
+                            for (int k = 0; k < PW; ++k) HR[jb][r + k] = hv[k];
+                        }
+                    }
+                    // the element as stored, or its mirror
+                    T d[4], tr[4];
+                    if (K == jb || (imag ? K < jb : K > jb))
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) d[r] = Sd[r * LS + 16 * jb];
+                    if (K == jb || (imag ? K > jb : K < jb)) {
+                        if (K < NB - 1) {
+                            const VL v = *reinterpret_cast<const VL*>(St + 16 * jb * LS);
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) tr[r] = v[r];
+                        } else {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) tr[r] = St[16 * jb * LS + r];
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int k = k0 + r;
+                        if (K == jb)
+                            X[jb][r] = imag ? -(k < jl ? d[r] : tr[r]) : k < jl ? tr[r] : (k > jl ? -d[r] : (T)0);
+                        else if (K < jb) X[jb][r] = imag ? -d[r] : tr[r];
+                        else X[jb][r] = imag ? -tr[r] : -d[r];
+                    }
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    HR[jb][r] = hv[r];
-                    const T d = Sd[(16 * K + r) * LS + 16 * jb];
-                    if (K < jb) {
-                        XA[jb][r] = d;
-                        XB[jb][r] = tr[r];
-                    } else if (K > jb) {
-                        XA[jb][r] = tr[r];
-                        XB[jb][r] = -d;
-                    } else {
-                        const int k = k0 + r;
-                        XA[jb][r] = k < jl ? d : tr[r];
-                        XB[jb][r] = k < jl ? tr[r] : (k > jl ? -d : (T)0);
-                    }
+                    if (r >= steps) break;
+#pragma unroll
+                    for (int a = 0; a < NB; ++a)
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) W[a * NB + b] = mfma16(HR[a][r], X[b][r], W[a * NB + b]);
                 }
             }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (r >= steps) break;
-#pragma unroll
-                for (int a = 0; a < NB; ++a)
-#pragma unroll
-                    for (int b = 0; b <= a; ++b) {
-                        const int x = a * (a + 1) / 2 + b;
-                        re[x] = mfma16(HR[a][r], XB[b][r], re[x]);
-                        im[x] = mfma16(HR[b][r], -XA[a][r], im[x]);
-                        re[x] = mfma16(XB[a][r], HR[b][r], re[x]);
-                        im[x] = mfma16(XA[b][r], HR[a][r], im[x]);
-                    }
-            }
-        }
-        // E R + (E R)^dagger, four links at a time
+        };
+        product(std::false_type{}, accU);
+        product(std::true_type{}, accV);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!kHlds) ra = rows(own_links, count, 0);
+        // the rows of four links at a time
         for (int q = 0;;) {
             T E[NB], xr[NB], xi[NB];
 #pragma unroll
@@ -394,12 +421,9 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
 #pragma unroll
             for (int a = 0; a < NB; ++a)
 #pragma unroll
-                for (int b = 0; b <= a; ++b) {
-                    const int x = a * (a + 1) / 2 + b;
-                    re[x] = mfma16(E[a], xr[b], re[x]);
-                    im[x] = mfma16(E[b], xi[a], im[x]);
-                    re[x] = mfma16(xr[a], E[b], re[x]);
-                    im[x] = mfma16(-xi[b], E[a], im[x]);
+                for (int b = 0; b < NB; ++b) {
+                    accU[a * NB + b] = mfma16(E[a], xr[b], accU[a * NB + b]);
+                    accV[a * NB + b] = mfma16(E[a], xi[b], accV[a * NB + b]);
                 }
             if (4 * ++q >= count) break;
             if constexpr (kRoom) {
@@ -414,7 +438,6 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
         if constexpr (kRoom)
             if (low) load(A.out + tile, plus);
         if constexpr (!kRoom) ahead = links(min(u + stride, t.n_ado - 1));
-        if constexpr (!kAhead && NBASE > 0) load(A.base + tile, bas);
         // w_in sigma + h (f - damping) at [j][i], in place of sigma
         fence();
 #pragma unroll
@@ -422,7 +445,7 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
 #pragma unroll
             for (int cb = 0; cb < NB; ++cb) {
                 if (cb == 0) __builtin_amdgcn_sched_barrier(0);
-                const int x = max(rb, cb) * (max(rb, cb) + 1) / 2 + min(rb, cb);
+                const int x = cb * NB + rb;  // U, accV[i][j]
                 const int j = 16 * rb + jl, i0 = 16 * cb + 4 * g;
                 T* at = S + (16 * rb + jl) * LS + 16 * cb + 4 * g;
                 const VL s = *reinterpret_cast<const VL*>(at);
@@ -432,10 +455,10 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     T f, gm = gam + di[r] + dj;
-                    if (cb > rb) f = re[x][r];
-                    else if (cb < rb) f = im[x][r];
+                    if (cb > rb) f = accU[x][r];
+                    else if (cb < rb) f = accV[x][r];
                     else {
-                        f = 4 * g + r >= jl ? re[x][r] : im[x][r];
+                        f = 4 * g + r >= jl ? accU[x][r] : accV[x][r];
                         if (4 * g + r == jl) gm = gam;
                     }
                     o[r] = A.w_in * s[r] + A.h * (f - gm * s[r]);
@@ -458,8 +481,32 @@ __global__ __launch_bounds__((packed_threads<T, NB>())) __attribute__((
                 }
             }
         fence();
-        // linear again: the bases, and what the next stages need
+        // the transposed halves, at [i][j]: U below P's diagonal's row, -V past it
+#pragma unroll
+        for (int rb = 0; rb < NB; ++rb) {
+            __builtin_amdgcn_sched_barrier(0);
+            T w[NB][4];
+#pragma unroll
+            for (int cb = 0; cb < NB; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) w[cb][r] = S[(16 * rb + 4 * g + r) * LS + 16 * cb + jl];
+#pragma unroll
+            for (int cb = 0; cb < NB; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int x = rb * NB + cb;
+                    T f = cb > rb ? accU[x][r] : -accV[x][r];
+                    if (cb == rb && jl >= 4 * g + r) f = accU[x][r];
+                    const bool inside = (rb < NB - 1 || 16 * rb + 4 * g + r < N) && (cb < NB - 1 || 16 * cb + jl < N);
+                    S[(16 * rb + 4 * g + r) * LS + 16 * cb + jl] = inside ? w[cb][r] + A.h * f : (T)0;
+                }
+        }
+        fence();
+        // linear again: the bases, and what the next stages need (the pieces'
+        // offsets computed anew: kept since the loads they spill)
         __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" : "+v"(lane));
+        if constexpr (!kAhead && NBASE > 0) load(A.base + tile, bas);
         if constexpr (ZOUT && !kRoom) load(A.in + tile, p);
         const bool again = low || A.side_out;
 #pragma unroll
@@ -691,7 +738,7 @@ hipError_t launch_k(int k, const Job& J, const StageSpec& sp, const PackedStage<
 
 template <typename T>
 hipError_t launch_nb(int k, const Job& J, const StageSpec& sp, const PackedStage<T>& A, hipStream_t stream) {
-    const bool va = J.t.N % (sizeof(T) == 4 || J.t.N > 32 ? 4 : 2) == 0;
+    const bool va = J.t.N % (16 / sizeof(T)) == 0;  // pieces do not cross rows
     switch ((J.t.N + 15) / 16) {
         case 1:
             if constexpr (sizeof(T) == 8)
@@ -721,6 +768,7 @@ hipError_t stage(int k, const Job& J, const PackedRun& R, const StageSpec& sp, h
     A.out = k == 1 ? b : k == 3 ? y : a;
     A.base = k == 3 ? z : y;
     A.z = z;
+    A.hop = static_cast<const T*>(R.h);
     const size_t plane = (size_t)J.n_low * N * N;
     T* m[2] = {static_cast<T*>(R.mirror[0]), static_cast<T*>(R.mirror[1])};
     A.mr_in = m[k & 1];
@@ -750,6 +798,10 @@ hipError_t begin(const Job& J, const PackedRun& R, hipStream_t stream) {
     const int N = J.t.N, n = J.t.n_ado - 1;
     T* mr = static_cast<T*>(R.mirror[0]);
     T* mi = mr + (size_t)J.n_low * N * N;
+    if (R.h) {
+        const int NB = (N + 15) / 16;
+        hipLaunchKernelGGL(k_h_operand, dim3(NB * NB), dim3(256), 0, stream, J.t, NB, static_cast<double*>(R.h));
+    }
     if (R.complex_rest)
         hipLaunchKernelGGL((k_pack<T>), dim3(n), dim3(256), N * (N + 1) * sizeof(T), stream, J.t, R.complex_rest,
                            static_cast<T*>(J.rest[0]), mr, mi, static_cast<T*>(R.side[0]), J.n_low);
@@ -786,6 +838,7 @@ bool packed_plan(const Job& J, int precision, size_t sigma0_bytes, size_t work_b
     for (int k = 0; k < 3; ++k) L->array[k] = take((size_t)n * NN * ts);
     for (int k = 0; k < 2; ++k) L->mirror[k] = take(2 * (size_t)J.n_low * NN * ts);
     if (precision != 2) L->y = take((size_t)n * NN * ts);
+    if (precision == 0 && t.N > 32) L->h = take(9 * 256 * ts);
     if (o > work_bytes) return false;
     // side rows where they fit too (a packed state leaves no room for them)
     if (precision != 2 && J.n_low > 0 && (n - J.n_low) * t.D < (int64_t(1) << 31)) {
