@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libheom.so")
-SOURCES = [os.path.join(CSRC, f) for f in ("heom_kernels.hip", "heom_packed.hip", "heom_resident.hip", "heom_host.cpp",
+SOURCES = [os.path.join(CSRC, f) for f in ("heom_kernels.hip", "heom_packed.hip", "heom_columns.hip", "heom_resident.hip", "heom_host.cpp",
                                            "heom_server.cpp", "heom_scratch.hip")]
 
 HIPCC_FLAGS = [

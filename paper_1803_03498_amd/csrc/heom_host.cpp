@@ -930,6 +930,17 @@ int64_t packed_min(int precision) {
     return precision == HEOM_FP64 ? 2000000 : precision == HEOM_FP32_HERM ? 1000000 : 8000000;
 }
 
+// Tiles (of 64 / N ADOs, one per wavefront) from which a hierarchy of 2 to 8
+// states takes the kernel of one column per lane: with fewer, its chains of
+// waits are not covered (us per step, one thread per element / one column per
+// lane: FP32 1856 tiles 89 / 118, 2544 tiles 126 / 115, 4307 tiles 170 / 155,
+// 6359 tiles 250 / 109; FP64 1609 tiles 152 / 164, 2544 tiles 191 / 139).
+thread_local int64_t t_columns_min = -1;  // this thread's bound instead, for tests
+int64_t columns_min(int precision) {
+    if (t_columns_min >= 0) return t_columns_min;
+    return precision == HEOM_FP64 ? 2048 : 2400;
+}
+
 // heom_propagate on a given workspace.  `timing` allows the benchmark event
 // timing (which creates HIP events) and `graphs` the step graph (which
 // allocates); the no-alloc entry point passes false for both.
@@ -997,8 +1008,13 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     heom::PackedLayout lay;
     heom::PackedRun pack{};
     const int64_t elements = (int64_t)(h->t.n_ado - 1) * N * N;
-    const bool packed = n_steps > 0 && tiles > 0 && elements >= packed_min(h->d.precision) && heom::packed_plan(j, h->d.precision, h->info.sigma0_bytes, need - records_bytes,
+    const bool packed = n_steps > 0 && tiles > 0 && elements >= packed_min(h->d.precision) &&
+                        heom::packed_plan(j, h->d.precision, h->info.sigma0_bytes, need - records_bytes,
                                           heom::control_bytes(N), &lay);
+    // small matrices: one column per lane, in tiles inside the run
+    const bool columns = n_steps > 0 && tiles > 0 && heom::columns_eligible(j, h->d.precision) &&
+                         (h->t.n_ado - 2) / (64 / N) + 1 >= columns_min(h->d.precision);
+    void* z = nullptr;
     if (packed) {
         for (int k = 0; k < 3; ++k) {
             j.sig0[k + 1] = w + lay.sig0[k];
@@ -1015,6 +1031,9 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
         }
         hipError_t e = heom::packed_begin(j, pack, h->d.precision, st);
         if (e != hipSuccess) return fail(HEOM_E_DEVICE, "pack launch: %s", hipGetErrorString(e));
+    } else if (columns) {
+        z = j.rest[3];
+        j.rest[3] = j.rest[1];
     } else if (h->d.precision == HEOM_FP32_HERM && j.n_low > 0 && tiles > 0) {
         // complex copies of the lower levels, alternating between the two
         // buffers: stage k reads the copy the previous stage wrote
@@ -1036,9 +1055,11 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
             const hipEvent_t begin = timed ? ev[2 * (step * 4 + k)] : nullptr;
             const hipEvent_t end = timed ? ev[2 * (step * 4 + k) + 1] : nullptr;
             hipError_t e = hipSuccess;
-            if (packed) {
+            if (packed || columns) {
                 if (begin) e = hipEventRecord(begin, s);
-                if (e == hipSuccess) e = heom::packed_stage(k, j, pack, h->d.precision, sp[k], s);
+                if (e == hipSuccess)
+                    e = packed ? heom::packed_stage(k, j, pack, h->d.precision, sp[k], s)
+                               : heom::columns_stage(k, j, z, step == done, step == n_steps - 1, h->d.precision, sp[k], s);
                 if (e == hipSuccess && end) e = hipEventRecord(end, s);
             } else {
                 e = heom::launch_stage(j, nullptr, 0, tiles, h->d.precision, sp[k], s, begin, end);
@@ -1062,7 +1083,8 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
                         hipGetErrorString(e));
         ++step;
         if (graph.capture([&](hipStream_t cs) { return launch_step(step, cs); })) {
-            for (; step < n_steps; ++step)
+            // (the last step of a run in tiles is a launch of its own)
+            for (; step < n_steps - (columns ? 1 : 0); ++step)
                 if ((e = hipGraphLaunch(graph.exec, st)) != hipSuccess)
                     return fail(HEOM_E_DEVICE, "graph launch: %s", hipGetErrorString(e));
         }
@@ -1125,6 +1147,9 @@ void heom_test_resident_wait(int64_t ticks) { t_resident_wait_ticks = ticks; }
 // Not part of the ABI: runs of this thread are packed from so many elements
 // on (< 0 = the library's choice).
 void heom_test_packed_min(int64_t elements) { t_packed_min = elements; }
+
+// Not part of the ABI: the same for the kernel of one column per lane, in tiles.
+void heom_test_columns_min(int64_t tiles) { t_columns_min = tiles; }
 
 heom_status heom_propagate_noalloc(const heom_hierarchy* h, heom_state io, double dt_fs,
                                    int64_t n_steps, int32_t record_every,

@@ -169,6 +169,12 @@ hipError_t packed_begin(const Job& j, const PackedRun& r, int precision, hipStre
 hipError_t packed_stage(int k, const Job& j, const PackedRun& r, int precision, const StageSpec& sp,
                         hipStream_t stream);
 hipError_t packed_end(const Job& j, const PackedRun& r, int precision, hipStream_t stream);
+// Propagation of large Hermitian hierarchies of 2 to 8 states
+// (heom_columns.hip): stage k of a step, Job::rest: y, Y2, Y3, Y4 = Y2.
+bool columns_eligible(const Job& j, int precision);
+// first, last: of the run (its ends are in the caller's order).
+hipError_t columns_stage(int k, const Job& j, void* z, bool first, bool last, int precision, const StageSpec& sp,
+                         hipStream_t stream);
 // The sigma_0 stage next to packed ADOs, in a launch of its own.
 hipError_t launch_sigma0_packed(const Job& j, int tsize, const StageSpec& sp, hipStream_t stream);
 

@@ -56,10 +56,21 @@ __device__ __forceinline__ T pk_nb(const NbSrc<T>& s, int nb, int r, int c) {
     return G(reinterpret_cast<const T*>(s.rest))[(size_t)(nb - 1) * s.N * s.N + (size_t)r * s.N + c];
 }
 
-// Element (r, c) of neighbour nb, from complex (PK false) or packed storage.
-template <typename T, bool PK>
-__device__ __forceinline__ cpx<T> nb_get(const NbSrc<T>& s, int nb, int r, int c) {
-    if constexpr (PK) {
+// Element of row r, column c of ADO u >= 1 where n ADOs lie in tiles of GA
+// consecutive ones, [row][ADO][column] (heom_columns.hip).
+__device__ __forceinline__ size_t tiled_at(int GA, int N, int u, int r, int c, int n) {
+    const int v = u - 1, first = v / GA * GA;
+    return (size_t)first * (N * N) + (uint32_t)(r * (min(GA, n - first) * N) + (v - first) * N + c);
+}
+
+// Element (r, c) of neighbour nb, from complex (PK false) or packed storage;
+// TILE > 0: complex, n ADOs in tiles of TILE.
+template <typename T, bool PK, int TILE = 0>
+__device__ __forceinline__ cpx<T> nb_get(const NbSrc<T>& s, int nb, int r, int c, int n = 0) {
+    if constexpr (TILE > 0) {
+        if (nb == 0) return load_nb<T>(s, 0, r, c);
+        return ld<T>(s.rest, tiled_at(TILE, s.N, nb, r, c, n));
+    } else if constexpr (PK) {
         if (nb == 0) return load_nb<T>(s, 0, r, c);
         const T x = pk_nb(s, nb, min(r, c), max(r, c)), y = pk_nb(s, nb, max(r, c), min(r, c));
         return {x, r < c ? y : (r > c ? -y : (T)0)};
@@ -176,7 +187,7 @@ __host__ __device__ inline Sigma0Lds sigma0_lds(int N, int W, int tsize, bool he
 // carries sigma_0 along (lds_cap: the LDS the launch provides).
 // HC: the job may have a complex H.  The loops stay rolled: the code also
 // runs inside the bulk kernels, whose occupancy its registers would cost.
-template <typename T, bool BATCHED, bool HC, bool PK = false>
+template <typename T, bool BATCHED, bool HC, bool PK = false, int TILE = 0>
 __device__ void sigma0_stage(const Job& single, const Job* jobs, int job, const StageSpec& sp,
                              unsigned lds_cap, char* smem_s0) {
     const Job& J = BATCHED ? jobs[job] : single;
@@ -216,7 +227,7 @@ __device__ void sigma0_stage(const Job& single, const Job* jobs, int job, const 
         for (int idx = tid; idx < W * N; idx += blockDim.x) {
             const int l = idx / N, c = idx - (idx / N) * N;
             const int site = G(t.mode_site)[l];
-            const cpx<T> r = nb_get<T, PK>(nbs, 1 + l, site, c);
+            const cpx<T> r = nb_get<T, PK, TILE>(nbs, 1 + l, site, c, t.n_ado - 1);
             sRows[2 * idx] = r.re;
             sRows[2 * idx + 1] = r.im;
             if (!herm) {
@@ -271,8 +282,8 @@ __device__ void sigma0_stage(const Job& single, const Job* jobs, int job, const 
                             x = {sCols[2 * (l * N + i)], sCols[2 * (l * N + i) + 1]};
                         }
                     } else {
-                        x = (herm && pass == 1) ? cconj(nb_get<T, PK>(nbs, 1 + l, s, i))
-                                                : nb_get<T, PK>(nbs, 1 + l, i, j);
+                        x = (herm && pass == 1) ? cconj(nb_get<T, PK, TILE>(nbs, 1 + l, s, i, t.n_ado - 1))
+                                                : nb_get<T, PK, TILE>(nbs, 1 + l, i, j, t.n_ado - 1);
                     }
                     const double pa = pass == 0 ? sPa[l] : -sPa[l];
                     fr -= pa * (double)x.im;
