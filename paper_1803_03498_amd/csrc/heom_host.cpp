@@ -1043,6 +1043,8 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
             sp[k].mirror_in = 1 + (k & 1);
             sp[k].mirror_out = 2 - (k & 1);
         }
+    } else {
+        heom::rk4_twelve(&j, h->d.precision, sp);
     }
     std::vector<hipEvent_t> ev;
     if (timed) {

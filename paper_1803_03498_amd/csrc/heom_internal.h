@@ -98,6 +98,11 @@ struct StageSpec {
     // `in` to read "-" rows from and of the copy of `out` to write (0 = none;
     // then "-" rows and columns are read from the packed ADOs).
     int32_t mirror_in, mirror_out;
+    // Matrix-core runs of 12 passes per step (rk4_twelve): the ADOs' stage 2
+    // also writes Z = (-y + Y2 + 2 Y3)/3 here, stage 4 is Y4/3 + Z + dt/6 f(Y4)
+    // (sigma_0 keeps the three bases above).
+    void* z_out;
+    const void* z_in;
 };
 
 // Resident propagation (heom_resident.hip): every step of a small hierarchy's
@@ -309,6 +314,7 @@ heom_status problem_rate_bound(const heom_problem* p, double* rate);
 bool block_step_ok(const heom_problem* p, double dt);
 double rk4_real_limit();
 void set_last_error(const std::string& msg);
-void rk4_stage_specs(StageSpec sp[4]);           // the four classic RK4 stages
+void rk4_stage_specs(StageSpec sp[4]);
+void rk4_twelve(Job* j, int precision, StageSpec sp[4]);           // the four classic RK4 stages
 double monotonic_seconds();
 }  // namespace heom

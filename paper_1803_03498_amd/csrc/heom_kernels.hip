@@ -1684,10 +1684,10 @@ static int resident_workgroups(const void* fn, int threads, size_t lds, int max_
     return per_cu * n_cu.load();
 }
 
-template <int NB, int NBASE, int VEC>
+template <int NB, int NBASE, bool ZOUT, int VEC>
 static hipError_t launch_persist_t(const Job& single, int total_tiles, const StageSpec& sp,
                                    hipStream_t stream) {
-    const void* fn = reinterpret_cast<const void*>(&k_stage_persist<NB, NBASE, VEC>);
+    const void* fn = reinterpret_cast<const void*>(&k_stage_persist<NB, NBASE, ZOUT, VEC>);
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     if (allow_full_lds(attr_once, attr_err, fn) != hipSuccess) return attr_err;
@@ -1711,7 +1711,7 @@ static hipError_t launch_persist_t(const Job& single, int total_tiles, const Sta
     if (e != hipSuccess) return e;
     int workers = std::min(total_tiles, resident_workgroups(fn, NT, lds, cap));
     if (g_max_workgroups.load() > 0) workers = std::min(workers, g_max_workgroups.load());
-    hipLaunchKernelGGL((k_stage_persist<NB, NBASE, VEC>), dim3(extra + workers), dim3(NT), lds,
+    hipLaunchKernelGGL((k_stage_persist<NB, NBASE, ZOUT, VEC>), dim3(extra + workers), dim3(NT), lds,
                        stream, single, sp, total_tiles, extra, (unsigned)lds);
     return hipGetLastError();
 }
@@ -1719,13 +1719,11 @@ static hipError_t launch_persist_t(const Job& single, int total_tiles, const Sta
 template <int NB, int VEC>
 static hipError_t launch_persist_vec(const Job& single, int total_tiles, const StageSpec& sp,
                                      hipStream_t stream) {
-    switch (sp.nbase) {
-        case 0: return launch_persist_t<NB, 0, VEC>(single, total_tiles, sp, stream);
-        case 1: return launch_persist_t<NB, 1, VEC>(single, total_tiles, sp, stream);
-        case 2: return launch_persist_t<NB, 2, VEC>(single, total_tiles, sp, stream);
-        case 3: return launch_persist_t<NB, 3, VEC>(single, total_tiles, sp, stream);
-        default: return hipErrorInvalidValue;
-    }
+    if (sp.z_in) return launch_persist_t<NB, 1, false, VEC>(single, total_tiles, sp, stream);
+    if (sp.nbase > 1 || (sp.nbase == 1 && sp.wbase[0] != 1.0)) return hipErrorInvalidValue;
+    if (sp.nbase == 0) return launch_persist_t<NB, 0, false, VEC>(single, total_tiles, sp, stream);
+    return sp.z_out ? launch_persist_t<NB, 1, true, VEC>(single, total_tiles, sp, stream)
+                    : launch_persist_t<NB, 1, false, VEC>(single, total_tiles, sp, stream);
 }
 
 template <int NB>
@@ -2015,6 +2013,15 @@ hipError_t launch_sigma0_packed(const Job& j, int tsize, const StageSpec& sp, hi
     const size_t lds = sigma0_lds(j.t.N, j.t.W, tsize, true, 160 * 1024).total;
     return tsize == 4 ? launch_sigma0_t<float, false, true>(j, nullptr, 1, sp, lds, stream)
                       : launch_sigma0_t<double, false, true>(j, nullptr, 1, sp, lds, stream);
+}
+
+// A run of single-job stages that the persistent matrix-core kernel takes moves
+// 12 passes per step: Z takes the place of Y4, which goes over Y2.
+void rk4_twelve(Job* j, int precision, StageSpec sp[4]) {
+    if (precision != 1 || persist_blocks(*j, false) == 0) return;
+    sp[1].z_out = j->rest[3];
+    sp[3].z_in = j->rest[3];
+    j->rest[3] = j->rest[1];
 }
 
 const char* last_launch_failure() { return g_launch_what; }

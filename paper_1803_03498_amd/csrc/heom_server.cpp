@@ -160,6 +160,7 @@ struct Group {
     bool solo = false;  // one job, launched on its own
     int job_off = 0, n_jobs = 0, tiles = 0;
     heom::Job sizing{};
+    heom::StageSpec sp[4];
 };
 
 }  // namespace
@@ -449,6 +450,7 @@ bool heom_server::rebuild() {
         g.job_off = off;
         g.n_jobs = (int)kv.second.size();
         g.sizing = *kv.second.front();
+        heom::rk4_stage_specs(g.sp);
         int maxN = 0, maxW = 0, maxD = 0, tiles = 0, any_hc = 0;
         size_t fma_bytes = 0;
         for (const heom::Job* j : kv.second) {
@@ -475,6 +477,7 @@ bool heom_server::rebuild() {
         if (g.nb == 0) g.sizing.t.h_complex = 1;  // selects the FMA path for any N
         if (g.solo) {
             g.sizing = *kv.second.front();  // the job itself, launched alone
+            heom::rk4_twelve(&g.sizing, g.precision, g.sp);
             g.tiles = g.sizing.t.n_ado > 1 ? g.sizing.n_tiles : 0;
         }
         groups.push_back(g);
@@ -501,7 +504,7 @@ bool heom_server::launch_macro_step() {
     for (int k = 0; k < 4 && e == hipSuccess; ++k) {
         for (const Group& g : groups) {
             e = heom::launch_stage(g.sizing, g.solo ? nullptr : jobs_dev + g.job_off,
-                                   g.solo ? 0 : g.n_jobs, g.tiles, g.precision, sp[k], stream);
+                                   g.solo ? 0 : g.n_jobs, g.tiles, g.precision, g.sp[k], stream);
             if (e != hipSuccess) break;
         }
         // every coherence-block request in one launch per stage
