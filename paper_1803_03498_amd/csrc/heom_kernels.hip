@@ -312,12 +312,10 @@ __global__ __launch_bounds__(kFmaMaxBlock) __attribute__((amdgpu_waves_per_eu(
     sizeof(T) == 4 ? 8 : 5))) void k_bulk_fma(Job single, const Job* jobs, int n_jobs, StageSpec sp,
                                               int s0_blocks, unsigned lds_total) {
     extern __shared__ char smem_raw[];
-    if constexpr (sizeof(T) == 4) {
-        if ((int)blockIdx.x < s0_blocks) {
-            // the first workgroups carry the sigma_0 stage along
-            sigma0_stage<T, BATCHED, HC>(single, jobs, blockIdx.x, sp, lds_total, smem_raw);
-            return;
-        }
+    if ((int)blockIdx.x < s0_blocks) {
+        // the first workgroups carry the sigma_0 stage along
+        sigma0_stage<T, BATCHED, HC>(single, jobs, blockIdx.x, sp, lds_total, smem_raw);
+        return;
     }
     const int n_first = BATCHED ? 0
                                 : min((single.n_low + single.ados_per_tile - 1) / single.ados_per_tile,
@@ -1783,12 +1781,14 @@ static hipError_t launch_fma_t(const Job& single, const Job* jobs_dev, int n_job
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     if (allow_full_lds(attr_once, attr_err, reinterpret_cast<const void*>(&k_bulk_fma<T, BATCHED, HC>)) != hipSuccess) return attr_err;
-    // FP32 only: the FP64 sigma_0 code would cost the FP64 kernel its
-    // occupancy.  Eight FP32 workgroups per CU leave 20 KiB of LDS each.
+    // Eight FP32 (five FP64) workgroups per CU leave 20 (32) KiB of LDS each.
+    // With its loops rolled the sigma_0 code fits the registers of either
+    // kernel (nine states, 7315 ADOs, FP64 right-hand side: 33.9 us with a
+    // launch of its own, 29.7 without).
     int extra = 0;
     size_t lds_launch = lds;
-    hipError_t e = sigma0_ride_along<T, BATCHED>(single, jobs_dev, n_jobs, n_s0, sizeof(T) == 4, sp,
-                                                 160 * 1024 / 8, stream, &extra, &lds_launch);
+    hipError_t e = sigma0_ride_along<T, BATCHED>(single, jobs_dev, n_jobs, n_s0, true, sp,
+                                                 160 * 1024 / (sizeof(T) == 4 ? 8 : 5), stream, &extra, &lds_launch);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_bulk_fma<T, BATCHED, HC>), dim3(total_tiles + extra), dim3(fma_block(sizeof(T), single.t.N)),
                        lds_launch, stream, single, jobs_dev, n_jobs, sp, extra, (unsigned)lds_launch);
