@@ -59,16 +59,20 @@ def _mix_largest():
 # the device sources that define each stage kernel (its own file and the
 # shared helpers and launchers)
 KERNEL_SOURCES = {
-    "k_stage_persist": ("heom_kernels.hip", "heom_stage_persist.inc"),
-    "k_stage_small": ("heom_kernels.hip", "heom_stage_small.inc"),
+    "k_stage_persist": ("heom_kernels.hip", "heom_stage_persist.inc", "heom_stage_common.h", "heom_device.h"),
+    "k_stage_small": ("heom_kernels.hip", "heom_stage_small.inc", "heom_stage_common.h", "heom_device.h"),
+    "k_packed": ("heom_packed.hip", "heom_stage_common.h", "heom_device.h"),
+    "k_columns": ("heom_columns.hip", "heom_stage_common.h", "heom_device.h"),
+    "k_resident": ("heom_resident.hip", "heom_stage_common.h", "heom_device.h"),
 }
+_OTHER_SOURCES = ("heom_kernels.hip", "heom_stage_common.h", "heom_device.h")
 
 
 def _kernel_source_digest(kernel):
     """SHA-256 over the device sources of `kernel`, in the order listed."""
     import hashlib
     h = hashlib.sha256()
-    for name in KERNEL_SOURCES.get(kernel, ("heom_kernels.hip",)):
+    for name in KERNEL_SOURCES.get(kernel, _OTHER_SOURCES):
         with open(os.path.join(ROOT, "paper_1803_03498_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
@@ -171,7 +175,19 @@ def _cpu_model():
 
 
 def _bulk_kernel_name(info, precision, N, heom):
-    """The stage kernel that propagates ADOs u >= 1 of a Hermitian run."""
+    """The stage kernel that propagates ADOs u >= 1 of a Hermitian run with a
+    real H (the library's rules, whose reasons stand beside them in
+    heom_host.cpp, heom_packed.hip and heom_resident.hip)."""
+    n = info["n_ado"]
+    elements = (n - 1) * N * N
+    fp64 = precision == heom.FP64
+    if precision != heom.FP32_HERM and N <= 22 and elements <= 256 * 2048:
+        return "k_resident"
+    if (10 if fp64 else 17) <= N <= (48 if fp64 else 64) and elements >= (
+            2000000 if fp64 else 1000000 if precision == heom.FP32_HERM else 8000000):
+        return "k_packed"
+    if precision != heom.FP32_HERM and 2 <= N <= 8 and (n - 2) // (64 // N) + 1 >= (2048 if fp64 else 2400):
+        return "k_columns"
     if precision == heom.FP32_MIXED and 10 <= N <= 64:
         return "k_stage_persist"
     if not info["bulk_kernel"]:
@@ -192,7 +208,8 @@ def _table_bytes_per_launch(kernel, n, W, D, fp64):
     Dm = max(D, 1)
     n_low = comb(W + D - 1, W) - 1 if D >= 1 and W >= 1 else 0
     w_bytes = 16 if fp64 else 8
-    per_ado = Dm * (8 + 4 + w_bytes) + 8 + (1 if kernel == "k_bulk_mfma" else 0)
+    link = 8 if kernel == "k_columns" else 8 + 4 + w_bytes  # weights and states by mode in LDS there
+    per_ado = Dm * link + 8 + (1 if kernel == "k_bulk_mfma" else 0)
     return float((n - 1) * per_ado + n_low * W * (4 + 8))
 
 
@@ -743,8 +760,8 @@ def main():
     elapsed = t1 - t0
     ms_per_step = 1e3 * elapsed / steps
     ado_updates = n * steps / elapsed
-    e = info["elem_bytes"]
-    step_bytes = 13.0 * ((n - 1) * N * N * e + N * N * 16)
+    # what the stages of this run move, neighbour rows counted once
+    step_bytes = kbytes.value / steps + 13.0 * N * N * 16
     hbm_gbs = step_bytes * steps / elapsed / 1e9
     avg_launch_s = ms.value / 1e3 / max(launches.value, 1)
     bytes_per_launch = kbytes.value / max(launches.value, 1)

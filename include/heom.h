@@ -321,9 +321,11 @@ heom_status heom_destroy(heom_hierarchy* h);
  * with a pair of HIP events recorded on the caller's stream and,
  * after its final synchronisation, adds their elapsed times.  heom_timing_read
  * returns the accumulated milliseconds, the number of launches and the
- * algorithmic bytes those launches move (per RK4 step: 13 passes over the
- * ADO array, i.e. 2/3/3/5 passes for stages 1..4; neighbour reads counted
- * once), and optionally resets the counters. */
+ * algorithmic bytes those launches move (neighbour reads counted once; per RK4
+ * step 13 passes over the ADO array, i.e. 2/3/3/5 for stages 1..4, or 12, i.e.
+ * 2/4/3/3, where stage 2 leaves the base of stage 4; half the array where a run
+ * keeps Hermitian ADOs packed; a run in one launch counts 13), and optionally
+ * resets the counters.  A packed stage includes its launch of "+" sums. */
 heom_status heom_timing_enable(int32_t enable);
 /* Launch-shape override, for tests and tuning (process-wide; 0 = the
  * library's choice).  max_workgroups caps the number of workers of the

@@ -1051,7 +1051,10 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
         ev.resize(2 * (size_t)n_steps * 4);
         for (auto& x : ev) HIP_TRY(hipEventCreate(&x));
     }
-    static const int kPasses[4] = {2, 3, 3, 5};
+    // passes over the ADO array per stage: y, Y2, Y3, Y4 kept, or Z (which
+    // stage 2 writes) in place of three bases in stage 4
+    const bool twelve = packed || columns || sp[3].z_in;
+    static const int kPasses[2][4] = {{2, 3, 3, 5}, {2, 4, 3, 3}};
     auto launch_step = [&](int64_t step, hipStream_t s) -> hipError_t {
         for (int k = 0; k < 4; ++k) {
             const hipEvent_t begin = timed ? ev[2 * (step * 4 + k)] : nullptr;
@@ -1112,13 +1115,13 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     HIP_TRY(hipStreamSynchronize(st));
     if (timed) {
         double ms_total = 0.0, bytes = 0.0;
-        const double pass = (double)h->info.rest_bytes;
+        const double pass = (double)h->info.rest_bytes / (pack.complex_rest ? 2 : 1);
         for (int64_t step = done; step < n_steps; ++step)
             for (int k = 0; k < 4; ++k) {
                 float ms = 0.0f;
                 HIP_TRY(hipEventElapsedTime(&ms, ev[2 * (step * 4 + k)], ev[2 * (step * 4 + k) + 1]));
                 ms_total += ms;
-                bytes += kPasses[k] * pass;
+                bytes += kPasses[twelve][k] * pass;
             }
         for (auto& x : ev) (void)hipEventDestroy(x);
         std::lock_guard<std::mutex> lk(g_timing.mu);

@@ -1718,6 +1718,8 @@ template <int NB, int VEC>
 static hipError_t launch_persist_vec(const Job& single, int total_tiles, const StageSpec& sp,
                                      hipStream_t stream) {
     if (sp.z_in) return launch_persist_t<NB, 1, false, VEC>(single, total_tiles, sp, stream);
+    if constexpr (NB >= 2)
+        if (sp.nbase == 3) return launch_persist_t<NB, 3, false, VEC>(single, total_tiles, sp, stream);
     if (sp.nbase > 1 || (sp.nbase == 1 && sp.wbase[0] != 1.0)) return hipErrorInvalidValue;
     if (sp.nbase == 0) return launch_persist_t<NB, 0, false, VEC>(single, total_tiles, sp, stream);
     return sp.z_out ? launch_persist_t<NB, 1, true, VEC>(single, total_tiles, sp, stream)
@@ -1737,7 +1739,7 @@ static hipError_t launch_persist_nb(const Job& single, int total_tiles, const St
 // too little of a 16 x 16 matrix-core tile, and tiles of several ADOs on the
 // FMA path are faster (the 12.3M-ADO (6, 6) FMO reference at N = 7: 17.8 ms
 // per stage here, 15.9 ms on the one-launch FMA kernel, 6.6 ms on the
-// persistent FMA kernel; at N = 14, 237k ADOs: 0.34 ms here against 0.49 ms
+// persistent FMA kernel; at N = 14, 237k ADOs: 0.31 ms here against 0.49 ms
 // on the persistent FMA kernel and 1.18 ms on the one-launch FMA kernel).
 static int persist_blocks(const Job& single, bool batched) {
     if (batched || single.herm == 0 || single.t.h_complex != 0 || single.t.N < 10 ||
@@ -2016,9 +2018,13 @@ hipError_t launch_sigma0_packed(const Job& j, int tsize, const StageSpec& sp, hi
 }
 
 // A run of single-job stages that the persistent matrix-core kernel takes moves
-// 12 passes per step: Z takes the place of Y4, which goes over Y2.
+// 12 passes per step: Z takes the place of Y4, which goes over Y2.  Above 16
+// states a few thousand ADOs lie in the caches, a stage is one round of waits,
+// and writing Z adds to one while three bases come in side by side (us per
+// step, 13 / 12 passes: 22 states, 1035 ADOs 78 / 80; 24 states, 2925 ADOs 105
+// / 107; 17 states, 7770 ADOs 146 / 142; 33 states, 7140 ADOs 399 / 368).
 void rk4_twelve(Job* j, int precision, StageSpec sp[4]) {
-    if (precision != 1 || persist_blocks(*j, false) == 0) return;
+    if (precision != 1 || persist_blocks(*j, false) == 0 || (j->t.N > 16 && j->t.n_ado < 4096)) return;
     sp[1].z_out = j->rest[3];
     sp[3].z_in = j->rest[3];
     j->rest[3] = j->rest[1];

@@ -1,7 +1,8 @@
 """FP32 Hermitian runs on the persistent matrix-core kernel (hierarchies too
 small for the packed form and too large for one launch) against the FP64
-oracle: stage 2 leaves the base of stage 4, for one to four row blocks, element
-pairs (even N) and single elements (odd N).
+oracle, for one to four row blocks, element pairs (even N) and single elements
+(odd N): with three bases in stage 4 (few ADOs of more than 16 states), and
+with the one that stage 2 leaves.
 
 Tolerance: 1e-5 of the largest element over 3 steps (FP32 storage)."""
 
@@ -16,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 # (N, baths, Matsubara terms, depth)
 SIZES = [(15, 15, 0, 4), (16, 16, 0, 4), (24, 5, 0, 3), (31, 4, 0, 3), (35, 2, 1, 3), (48, 4, 0, 2), (63, 3, 0, 2),
-         (64, 3, 0, 2)]
+         (64, 3, 0, 2), (18, 8, 1, 4), (35, 28, 0, 3), (50, 28, 0, 3), (51, 28, 0, 3)]
 
 
 @pytest.mark.parametrize("size", SIZES, ids=[str(s) for s in SIZES])
