@@ -208,7 +208,8 @@ heom_status heom_rhs(const heom_hierarchy* h, heom_state in, heom_state out, int
  *   Y2 = y + dt/2 f(y), Y3 = y + dt/2 f(Y2), Y4 = y + dt f(Y3),
  *   y' = (-y + Y2 + 2 Y3 + Y4)/3 + dt/6 f(Y4),
  * the textbook step rewritten so that each stage reads one ADO array with its
- * neighbours and writes the next.  work_dev (heom_propagate_work_bytes) holds
+ * neighbours and writes the next (in some forms stage 2 also writes
+ * (-y + Y2 + 2 Y3)/3, the base of the last stage).  work_dev (heom_propagate_work_bytes) holds
  * the three stage copies, the records and a status word.  Observables of
  * sigma_0 are reduced in FP64 at step 0 and every record_every steps.
  * hermitian: as for heom_rhs, for the initial state (it is preserved).
@@ -218,8 +219,10 @@ heom_status heom_rhs(const heom_hierarchy* h, heom_state in, heom_state out, int
  * HEOM_E_NUMERIC if a recorded observable was not finite.  Small hierarchies
  * (HEOM_FP64 and HEOM_FP32_MIXED, N <= 22, up to about 255 workgroups of 2048
  * elements) run all their steps in one launch that keeps the state on the
- * compute units.  Of the others, runs of 8 steps
- * or more launch the first step directly and replay a HIP graph of one step
+ * compute units.  Large Hermitian runs (real H) keep their ADOs packed, or for
+ * N <= 8 in another order, inside the call: io.rest holds the state again when
+ * it returns HEOM_OK or HEOM_E_NUMERIC.  Stage by stage, runs of 8 steps or
+ * more launch the first step directly and replay a HIP graph of one step
  * (captured on a private stream) for the rest, unless kernel timing is on
  * (heom_timing_enable); the results are the same either way, bit for bit. */
 heom_status heom_propagate(const heom_hierarchy* h, heom_state io, void* work_dev,
