@@ -217,8 +217,8 @@ heom_status heom_rhs(const heom_hierarchy* h, heom_state in, heom_state out, int
  * the records are copied to host_out [n_rec][heom_record_doubles].
  * HEOM_E_UNSTABLE if dt exceeds the RK4 bound for the problem's rates;
  * HEOM_E_NUMERIC if a recorded observable was not finite.  Small hierarchies
- * (HEOM_FP64 and HEOM_FP32_MIXED, N <= 22, up to about 255 workgroups of 2048
- * elements) run all their steps in one launch that keeps the state on the
+ * (HEOM_FP64, Hermitian HEOM_FP32_MIXED; N <= 22, up to about 255 workgroups of
+ * 2048 elements) run all their steps in one launch that keeps the state on the
  * compute units.  Large Hermitian runs (real H) keep their ADOs packed, or for
  * N <= 8 in another order, inside the call: io.rest holds the state again when
  * it returns HEOM_OK or HEOM_E_NUMERIC.  Stage by stage, runs of 8 steps or

@@ -988,7 +988,11 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     heom::ResidentPlan plan;
     int64_t done = 0;
     int32_t status = 0;
-    if (n_steps > 0 && h->d.precision != HEOM_FP32_HERM &&
+    // FP32 runs of ADOs that are not Hermitian (dipole responses of a filled
+    // hierarchy) stay with the stage kernels: their FP64 sigma_0 shows the last
+    // FP32 bits of the ADOs, which another order of the same sums changes by
+    // 1e-9 and more of it
+    if (n_steps > 0 && h->d.precision != HEOM_FP32_HERM && (hermitian || h->d.precision == HEOM_FP64) &&
         heom::resident_plan(j, h->d.precision == HEOM_FP64 ? 8 : 4, &plan)) {
         s = resident_run(h, j, plan, w, ctl, ctl_bytes, n_steps, timed, host_out, n_rec * rd, st, &done,
                          &status);
