@@ -184,7 +184,7 @@ def _bulk_kernel_name(info, precision, N, heom):
     if precision != heom.FP32_HERM and N <= 22 and elements <= 256 * 2048:
         return "k_resident"
     if (10 if fp64 else 17) <= N <= (48 if fp64 else 64) and elements >= (
-            2000000 if fp64 else 1000000 if precision == heom.FP32_HERM else 8000000):
+            (600000 if N < 16 else 1600000) if fp64 else 1500000 if precision == heom.FP32_HERM else 7000000):
         return "k_packed"
     if precision != heom.FP32_HERM and 2 <= N <= 8 and (n - 2) // (64 // N) + 1 >= (2048 if fp64 else 2400):
         return "k_columns"

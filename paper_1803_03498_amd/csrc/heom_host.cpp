@@ -919,15 +919,18 @@ heom_status resident_run(const heom_hierarchy* h, const heom::Job& j, const heom
 
 // Elements of the ADO array from which a Hermitian run is packed.  Below,
 // the extra launches ("+" sums, pack, unpack) and one wavefront per ADO cost
-// more than the halved bytes give (us per step, complex / packed: FP32 40
-// states, 3321 ADOs 244 / 285, 24 states, 20475 ADOs 323 / 304, 48 states,
-// 20825 ADOs 1208 / 861; FP64 24 states, 2925 ADOs 143 / 151, 17 states, 7770
-// ADOs 264 / 191; packed storage, 33 states, 595 ADOs 108 / 163 and 31
-// states, 2016 ADOs 202 / 149).
+// more than the halved bytes give (us per step, unpacked / packed: FP32 40
+// states, 3321 ADOs 260 / 278, 33 states, 7140 ADOs 364 / 283, 24 states, 20475
+// ADOs 329 / 279; FP64 24 states, 2925 ADOs 153 / 152, 17 states, 5985 ADOs 228
+// / 155, 36 states, 703 ADOs 163 / 192; packed storage, 23 states, 2600 ADOs 104
+// / 108, 24 states, 2925 ADOs 120 / 109).  FP64 below 16 states would take the
+// FMA kernels instead (14 states, 3060 ADOs 139 / 77; 16 states, 4845 ADOs, on
+// the matrix cores either way, 94 / 99).
 thread_local int64_t t_packed_min = -1;  // this thread's bound instead, for tests
-int64_t packed_min(int precision) {
+int64_t packed_min(int precision, int N) {
     if (t_packed_min >= 0) return t_packed_min;
-    return precision == HEOM_FP64 ? 2000000 : precision == HEOM_FP32_HERM ? 1000000 : 8000000;
+    if (precision == HEOM_FP64) return N < 16 ? 600000 : 1600000;
+    return precision == HEOM_FP32_HERM ? 1500000 : 7000000;
 }
 
 // Tiles (of 64 / N ADOs, one per wavefront) from which a hierarchy of 2 to 8
@@ -1012,7 +1015,7 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     heom::PackedLayout lay;
     heom::PackedRun pack{};
     const int64_t elements = (int64_t)(h->t.n_ado - 1) * N * N;
-    const bool packed = n_steps > 0 && tiles > 0 && elements >= packed_min(h->d.precision) &&
+    const bool packed = n_steps > 0 && tiles > 0 && elements >= packed_min(h->d.precision, N) &&
                         heom::packed_plan(j, h->d.precision, h->info.sigma0_bytes, need - records_bytes,
                                           heom::control_bytes(N), &lay);
     // small matrices: one column per lane, in tiles inside the run
