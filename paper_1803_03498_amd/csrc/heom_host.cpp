@@ -864,30 +864,36 @@ hipError_t resident_launches(heom::ResidentArgs& a, bool grid, int64_t n_steps, 
     return hipSuccess;
 }
 
-// The run by resident launches.  Workspace: control block (commit word at
-// 512) | flags | two sigma_0 copies | two stage copies.  *done: committed
-// steps; fewer than n_steps if a launch gave up.
+// Whether a run takes resident launches, and how.  FP32 runs of ADOs that are
+// not Hermitian (dipole responses of a filled hierarchy) stay with the stage
+// kernels: their FP64 sigma_0 shows the last FP32 bits of the ADOs, which
+// another order of the same sums changes by 1e-9 and more of it.  stage_bytes:
+// the workspace in front of the records.
+bool resident_takes(const heom::Job& j, int precision, const heom_info& info, size_t stage_bytes,
+                    heom::ResidentPlan* plan, heom::ResidentLayout* lay) {
+    return precision != HEOM_FP32_HERM && (j.herm || precision == HEOM_FP64) &&
+           heom::resident_plan(j, precision == HEOM_FP64 ? 8 : 4, plan) &&
+           heom::resident_layout(*plan, info.sigma0_bytes, info.rest_bytes, heom::control_bytes(j.t.N),
+                                 stage_bytes, lay);
+}
+
+// The run by resident launches (control block: commit word at 512).  *done:
+// committed steps; fewer than n_steps if a launch gave up.
 heom_status resident_run(const heom_hierarchy* h, const heom::Job& j, const heom::ResidentPlan& plan,
-                         char* w, const char* ctl, size_t ctl_bytes, int64_t n_steps, bool timed,
-                         double* host_out, int64_t out_doubles, hipStream_t st, int64_t* done,
+                         const heom::ResidentLayout& lay, char* w, const char* ctl, int64_t n_steps,
+                         bool timed, double* host_out, int64_t out_doubles, hipStream_t st, int64_t* done,
                          int32_t* status) {
     heom::ResidentArgs a{};
-    char* at = w + ctl_bytes;
     if (plan.grid) {
-        a.flags = reinterpret_cast<uint32_t*>(at);
-        at += kResidentFlagBytes;
+        a.flags = reinterpret_cast<uint32_t*>(w + lay.flags);
         for (int k = 0; k < 2; ++k) {
-            a.s0x[k] = at;
-            at += align256(h->info.sigma0_bytes);
-        }
-        for (int k = 0; k < 2; ++k) {
-            a.exch[k] = at;
-            at += align256(h->info.rest_bytes);
+            a.s0x[k] = w + lay.s0x[k];
+            a.exch[k] = w + lay.exch[k];
         }
     }
     a.commit = reinterpret_cast<uint32_t*>(w + 512);
-    HIP_TRY(hipMemcpyAsync(w, ctl, ctl_bytes + (plan.grid ? kResidentFlagBytes : 0),
-                           hipMemcpyHostToDevice, st));
+    // the flags, if any, lie right behind the control block
+    HIP_TRY(hipMemcpyAsync(w, ctl, heom::control_bytes(h->t.N) + lay.flag_bytes, hipMemcpyHostToDevice, st));
     hipEvent_t ev[2] = {nullptr, nullptr};
     if (timed)
         for (auto& e : ev) HIP_TRY(hipEventCreate(&e));
@@ -989,16 +995,11 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     const int tiles = h->t.n_ado > 1 ? j.n_tiles : 0;
     const bool timed = timing && g_timing.enabled.load() && tiles > 0;
     heom::ResidentPlan plan;
+    heom::ResidentLayout res;
     int64_t done = 0;
     int32_t status = 0;
-    // FP32 runs of ADOs that are not Hermitian (dipole responses of a filled
-    // hierarchy) stay with the stage kernels: their FP64 sigma_0 shows the last
-    // FP32 bits of the ADOs, which another order of the same sums changes by
-    // 1e-9 and more of it
-    if (n_steps > 0 && h->d.precision != HEOM_FP32_HERM && (hermitian || h->d.precision == HEOM_FP64) &&
-        heom::resident_plan(j, h->d.precision == HEOM_FP64 ? 8 : 4, &plan)) {
-        s = resident_run(h, j, plan, w, ctl, ctl_bytes, n_steps, timed, host_out, n_rec * rd, st, &done,
-                         &status);
+    if (n_steps > 0 && resident_takes(j, h->d.precision, h->info, need - records_bytes, &plan, &res)) {
+        s = resident_run(h, j, plan, res, w, ctl, n_steps, timed, host_out, n_rec * rd, st, &done, &status);
         if (s != HEOM_OK || done == n_steps) return s;
         // given up (the GPU could not hold the launch): the stage kernels go
         // on from the last committed step
@@ -1155,6 +1156,31 @@ heom_status heom_propagate(const heom_hierarchy* h, heom_state io, void* work_de
 // Not part of the ABI: bounds the waits of this thread's resident launches
 // (100 MHz ticks; 0 = the first unanswered poll gives up, < 0 = the default).
 void heom_test_resident_wait(int64_t ticks) { t_resident_wait_ticks = ticks; }
+
+// Not part of the ABI, host only: how a run of `problem` is done: 0 = stage by
+// stage, 1 = one workgroup, 2 = a grid; out = end of what its launches use of the
+// workspace in front of the records, the size of that, LDS bytes per workgroup,
+// workgroups.
+int32_t heom_test_resident_plan(const heom_problem* problem, int32_t hermitian, size_t out[4]) {
+    heom_hierarchy h{};
+    if (derive(problem, h.d) != HEOM_OK) return -1;
+    fill_info(h.d, &h.info);
+    h.t.N = h.d.N;
+    h.t.W = h.d.W;
+    h.t.D = h.d.D;
+    h.t.n_ado = (int32_t)h.d.n_ado;
+    h.t.h_complex = h.d.h_complex ? 1 : 0;
+    heom::Job j = base_job(&h);
+    j.herm = hermitian ? 1 : 0;
+    heom::ResidentPlan plan;
+    heom::ResidentLayout lay;
+    if (!resident_takes(j, h.d.precision, h.info, h.info.work_bytes, &plan, &lay)) return 0;
+    out[0] = lay.end;
+    out[1] = h.info.work_bytes;
+    out[2] = plan.lds;
+    out[3] = (size_t)plan.groups + (plan.grid ? 1 : 0);
+    return plan.grid ? 2 : 1;
+}
 
 // Not part of the ABI: runs of this thread are packed from so many elements
 // on (< 0 = the library's choice).

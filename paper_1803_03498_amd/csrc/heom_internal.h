@@ -126,13 +126,23 @@ struct ResidentArgs {
     int64_t n_steps, step0;       // steps of this launch, and those done before it
     void* exch[2];                // stage outputs in turn: [n_ado-1][N][N]
     void* s0x[2];                 // the same for sigma_0: complex128 [N][N]
-    uint32_t* flags;              // [256] at kResidentFlagStride, below epoch0 + 1 before the launch
+    uint32_t* flags;              // [members] at kResidentFlagStride, below epoch0 + 1 before the launch
     uint32_t epoch0;              // stages of the launches before
     uint32_t* commit;             // `chunk` before the launch; chunk + 1 = done, or kResidentAborted
     uint32_t chunk;
     uint64_t wait_ticks;          // bound of each wait, ticks of the 100 MHz clock
 };
 bool resident_plan(const Job& j, int tsize, ResidentPlan* plan);
+// Where a run's launches keep what travels between workgroups: offsets into
+// the propagation workspace, behind the control block.  false: the `end` of it
+// lies past the stage copies (`work_bytes`), and the run is not a resident one.
+struct ResidentLayout {
+    size_t flags, flag_bytes;     // one flag per workgroup of the launch
+    size_t s0x[2], exch[2];
+    size_t end;
+};
+bool resident_layout(const ResidentPlan& plan, size_t sigma0_bytes, size_t rest_bytes, size_t offset,
+                     size_t work_bytes, ResidentLayout* layout);
 hipError_t launch_resident(const Job& j, const ResidentArgs& args, const ResidentPlan& plan,
                            int precision, hipStream_t stream);
 // The coherence-block form the same way.

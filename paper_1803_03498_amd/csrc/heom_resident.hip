@@ -918,6 +918,29 @@ bool resident_plan(const Job& J, int tsize, ResidentPlan* p) {
     return p->lds <= kGridLds;
 }
 
+// A workspace has room for three copies of sigma_0 and of the ADOs, and the
+// records behind them.  A grid takes two of each and its flags, 64 bytes per
+// workgroup: more than the third copies hold where the ADOs are 1 x 1 or 2 x 2
+// in FP32 and few enough (481 to 503 of them at 2 x 2, for instance).
+bool resident_layout(const ResidentPlan& p, size_t sigma0_bytes, size_t rest_bytes, size_t offset,
+                     size_t work_bytes, ResidentLayout* L) {
+    *L = ResidentLayout{};
+    size_t o = offset;
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o = (o + bytes + 255) & ~size_t(255);
+        return at;
+    };
+    if (p.grid) {
+        L->flag_bytes = (size_t)(p.groups + 1) * kResidentFlagStride * 4;
+        L->flags = take(L->flag_bytes);
+        for (int k = 0; k < 2; ++k) L->s0x[k] = take(sigma0_bytes);
+        for (int k = 0; k < 2; ++k) L->exch[k] = take(rest_bytes);
+    }
+    L->end = o;
+    return o <= work_bytes;
+}
+
 hipError_t launch_resident(const Job& J, const ResidentArgs& args, const ResidentPlan& p, int precision,
                            hipStream_t stream) {
     ResidentArgs A = args;
