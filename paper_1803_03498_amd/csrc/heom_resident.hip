@@ -13,10 +13,10 @@
 // Two forms:
 //   one workgroup (GRID = false): the hierarchy lives in LDS, the barrier is
 //     the workgroup's own.  Dimer (10 ADOs), FP64: 44 -> ~2 us per step.
-//   a grid (GRID = true): at most 256 workgroups of 512 threads, group 0 for
-//     sigma_0 and the observables, the others for the ADOs u >= 1, dealt out
-//     one by one (u = 1 + w + g G) so that the ADOs below the top level, which
-//     carry the "+" links, spread evenly.
+//   a grid (GRID = true): at most 256 workgroups of 256 to 768 threads, group
+//     0 for sigma_0 and the observables, the others for the ADOs u >= 1, dealt
+//     out one by one (u = 1 + w + g G) so that the ADOs below the top level,
+//     which carry the "+" links, spread evenly.
 //
 // Exchange without cache maintenance.  The eight XCDs have an L2 each, and
 // device-scope fences write back and invalidate it: 17 us per barrier of 256
@@ -30,10 +30,11 @@
 // their coupling terms from there (loading them element by element, each row
 // twice: 5.3 against 3.9 us per stage on 3060 ADOs of 7 x 7 in FP32).
 //
-// Progress.  A launch has at most 256 workgroups of 512 threads, 80 KiB of
-// LDS and 128 registers per thread: two of them fit the 256 CUs together, and
-// the host lets at most two run at once (ResidentPermit), so every workgroup
-// becomes resident.  Should one still be kept out (other processes on the
+// Progress.  A launch has at most 256 workgroups, each within half a CU: 80 KiB
+// of LDS (the static word included), and 768 threads of 80 registers (six waves
+// per SIMD) or 512 of 128 (four).  So two launches of either shape fit the 256
+// CUs together, and the host lets at most two run at once (ResidentPermit): every
+// workgroup becomes resident.  Should one still be kept out (other processes on the
 // GPU), each wait ends after `wait_ticks`, and the workgroups agree through
 // one word, by compare and swap, whether the launch commits or aborts.  The
 // caller's state is written only after a commit, so the host can run an
@@ -50,7 +51,9 @@ namespace heom {
 namespace {
 
 constexpr int kGridMax = 256;  // workgroups of a launch, sigma_0's included
-constexpr size_t kGridLds = 80 * 1024, kOneLds = 150 * 1024;
+// dynamic LDS; the kernels' static word takes 16 bytes with its alignment (10
+// states of one mode at depth 135 would ask for the full 80 KiB)
+constexpr size_t kStaticLds = 16, kGridLds = 80 * 1024 - kStaticLds, kOneLds = 150 * 1024;
 
 // LDS carve-up (bytes): bulk part, and sigma_0 part from its own base.  The
 // coupling lines of an element are a list of (element, complex weight)

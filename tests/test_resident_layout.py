@@ -63,3 +63,20 @@ def test_small_grids_keep_their_form(plan):
     for N, nb, M, D, precision, route in ((12, 12, 0, 1, 1, 2), (20, 3, 0, 1, 1, 2), (3, 3, 2, 3, 1, 2),
                                           (2, 2, 0, 16, 0, 2), (2, 2, 1, 8, 1, 0)):
         assert plan(hi.random_problem(1, N, n_baths=nb, M=M, D=D), precision)[0] == route, (N, nb, M, D)
+
+
+def test_two_grid_launches_fit_the_gpu(plan):
+    """Two workgroups fit a CU's 160 KiB of LDS, the launch's static word (16
+    bytes with its alignment) included: two launches can be on the GPU together."""
+    most = 0
+    for N, W, D in _sizes():
+        prob = {"H": np.zeros((N, N)), "temperature_K": 300.0, "depth": D, "flags": 0,
+                "baths": [{"state": s % N, "lambda_cm": 35.0, "tau_fs": 50.0, "matsubara": 0} for s in range(W)]}
+        for precision in (0, 1):
+            for herm in ((True, False) if precision == 0 else (True,)):
+                route, (_, _, lds, groups), _ = plan(prob, precision, herm)
+                if route == 2:
+                    most = max(most, lds)
+                    assert 2 * (lds + 16) <= 160 * 1024, (N, W, D, precision, herm)
+                    assert groups <= 256
+    assert most > 78 * 1024  # the bound is reached
