@@ -1309,7 +1309,13 @@ heom_status heom_propagate_block(const heom_hierarchy* h, void* state, void* wor
     hipError_t e = hipSuccess;
     int64_t done = 0;
     heom::ResidentPlan plan;
-    if (n_steps > 0 && heom::resident_block_plan(h->t, (int)h->d.n_low, &plan) &&
+    // A grid's launch builds its link lists first, which a step or two do not
+    // pay for (us per call, stage by stage / one launch: one step of 7 states,
+    // 3060 ADOs 100 / 112, 24 states, 325 ADOs 107 / 111, 40 states, 861 ADOs 125
+    // / 119; four elements per thread, 10 states, 10626 ADOs: one step 116 / 142,
+    // two 165 / 173, three 215 / 205).  Either way gives the same bits.
+    auto pays = [&] { return !plan.grid || n_steps >= (plan.ept == 4 ? 3 : N <= 32 ? 2 : 1); };
+    if (n_steps > 0 && heom::resident_block_plan(h->t, (int)h->d.n_low, &plan) && pays() &&
         (!plan.grid || copy >= kResidentFlagBytes)) {
         heom::ResidentArgs a{};
         a.commit = reinterpret_cast<uint32_t*>(w + 16);
