@@ -1783,14 +1783,26 @@ static hipError_t launch_fma_t(const Job& single, const Job* jobs_dev, int n_job
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     if (allow_full_lds(attr_once, attr_err, reinterpret_cast<const void*>(&k_bulk_fma<T, BATCHED, HC>)) != hipSuccess) return attr_err;
-    // Eight FP32 (five FP64) workgroups per CU leave 20 (32) KiB of LDS each.
     // With its loops rolled the sigma_0 code fits the registers of either
     // kernel (nine states, 7315 ADOs, FP64 right-hand side: 33.9 us with a
-    // launch of its own, 29.7 without).
+    // launch of its own, 28.9 without).  Registers allow 32 FP32 (20 FP64)
+    // waves per CU: LDS grows for sigma_0 to what leaves room for as many, or,
+    // in an FP64 launch whose workgroups are on the GPU at once anyway, to 32 KiB
+    // (with 32 KiB in every FP64 launch, one wavefront per workgroup, complex H:
+    // 20 states, 10626 ADOs 248 us, 185 this way, 196 with a launch of its own; 14
+    // states, 11628 ADOs 107, 83 and 89).
+    const int threads = fma_block(sizeof(T), single.t.N), per_cu = (sizeof(T) == 4 ? 32 : 20) * 64 / threads;
+    const bool at_once = sizeof(T) == 8 && total_tiles <= 5 * 256;
+    const size_t budget = at_once ? 32 * 1024 : 160 * 1024 / per_cu;
+    // Above 48 states the rows that sigma_0's "+" lines read do not fit.  Next to
+    // the short stages of few ADOs with a real H its wavefront would be the last
+    // one running where there are more modes than states (60 states, 150 modes,
+    // depth 1: 400 us against 309; 52 states, 52 modes 198 either way).
+    const bool late = at_once && !HC && single.t.N > 48 && single.t.W > single.t.N;
     int extra = 0;
     size_t lds_launch = lds;
-    hipError_t e = sigma0_ride_along<T, BATCHED>(single, jobs_dev, n_jobs, n_s0, true, sp,
-                                                 160 * 1024 / (sizeof(T) == 4 ? 8 : 5), stream, &extra, &lds_launch);
+    hipError_t e = sigma0_ride_along<T, BATCHED>(single, jobs_dev, n_jobs, n_s0, !late, sp, budget, stream, &extra,
+                                                 &lds_launch);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_bulk_fma<T, BATCHED, HC>), dim3(total_tiles + extra), dim3(fma_block(sizeof(T), single.t.N)),
                        lds_launch, stream, single, jobs_dev, n_jobs, sp, extra, (unsigned)lds_launch);
