@@ -842,6 +842,7 @@ constexpr int64_t kResidentSteps = 4096;
 constexpr uint64_t kResidentWaitTicks = 20000000ull;
 // this thread's bound instead, for tests of a launch that gives up
 thread_local int64_t t_resident_wait_ticks = -1;
+thread_local bool t_resident_off = false;  // this thread's runs take the other forms, for tests
 using heom::kResidentFlagBytes;
 
 // n_steps by launches of at most kResidentSteps, each a call of launch(last)
@@ -871,7 +872,7 @@ hipError_t resident_launches(heom::ResidentArgs& a, bool grid, int64_t n_steps, 
 // the workspace in front of the records.
 bool resident_takes(const heom::Job& j, int precision, const heom_info& info, size_t stage_bytes,
                     heom::ResidentPlan* plan, heom::ResidentLayout* lay) {
-    return precision != HEOM_FP32_HERM && (j.herm || precision == HEOM_FP64) &&
+    return !t_resident_off && precision != HEOM_FP32_HERM && (j.herm || precision == HEOM_FP64) &&
            heom::resident_plan(j, precision == HEOM_FP64 ? 8 : 4, plan) &&
            heom::resident_layout(*plan, info.sigma0_bytes, info.rest_bytes, heom::control_bytes(j.t.N),
                                  stage_bytes, lay);
@@ -960,6 +961,35 @@ int64_t columns_min(int precision) {
     return precision == HEOM_FP64 ? 2048 : 2400;
 }
 
+// How a run of at least one step is done.
+enum class RunForm { kStages, kResident, kPacked, kColumns };
+struct RunPlan {
+    RunForm form = RunForm::kStages;
+    heom::ResidentPlan resident;
+    heom::ResidentLayout resident_lay;
+    heom::PackedLayout packed_lay;
+};
+
+// stage_bytes: the workspace in front of the records.
+RunPlan run_plan(const heom::Job& j, int precision, const heom_info& info, size_t stage_bytes, bool resident) {
+    RunPlan p;
+    const int N = j.t.N;
+    if (j.t.n_ado < 2) return p;
+    if (resident && resident_takes(j, precision, info, stage_bytes, &p.resident, &p.resident_lay)) {
+        p.form = RunForm::kResident;
+    } else if ((int64_t)(j.t.n_ado - 1) * N * N >= packed_min(precision, N) &&
+               heom::packed_plan(j, precision, info.sigma0_bytes, stage_bytes, heom::control_bytes(N),
+                                 &p.packed_lay)) {
+        // large Hermitian runs keep their ADOs packed between the first and the
+        // last step
+        p.form = RunForm::kPacked;
+    } else if (heom::columns_eligible(j, precision) && (j.t.n_ado - 2) / (64 / N) + 1 >= columns_min(precision)) {
+        // small matrices: one column per lane, in tiles inside the run
+        p.form = RunForm::kColumns;
+    }
+    return p;
+}
+
 // heom_propagate on a given workspace.  `timing` allows the benchmark event
 // timing (which creates HIP events) and `graphs` the step graph (which
 // allocates); the no-alloc entry point passes false for both.
@@ -1003,15 +1033,17 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
 
     const int tiles = h->t.n_ado > 1 ? j.n_tiles : 0;
     const bool timed = timing && g_timing.enabled.load() && tiles > 0;
-    heom::ResidentPlan plan;
-    heom::ResidentLayout res;
     int64_t done = 0;
     int32_t status = 0;
-    if (n_steps > 0 && resident_takes(j, h->d.precision, h->info, need - records_bytes, &plan, &res)) {
-        s = resident_run(h, j, plan, res, w, ctl, n_steps, timed, host_out, n_rec * rd, st, &done, &status);
+    RunPlan plan;
+    if (n_steps > 0) plan = run_plan(j, h->d.precision, h->info, need - records_bytes, true);
+    if (plan.form == RunForm::kResident) {
+        s = resident_run(h, j, plan.resident, plan.resident_lay, w, ctl, n_steps, timed, host_out, n_rec * rd, st,
+                         &done, &status);
         if (s != HEOM_OK || done == n_steps) return s;
         // given up (the GPU could not hold the launch): the stage kernels go
         // on from the last committed step
+        plan = run_plan(j, h->d.precision, h->info, need - records_bytes, false);
     }
     std::memcpy(ctl, &done, 8);
     std::memcpy(ctl + 256, &status, 4);
@@ -1020,17 +1052,9 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     heom::StageSpec sp[4];
     heom::rk4_stage_specs(sp);
 
-    // large Hermitian runs keep their ADOs packed between the first and the
-    // last step
-    heom::PackedLayout lay;
+    const bool packed = plan.form == RunForm::kPacked, columns = plan.form == RunForm::kColumns;
+    const heom::PackedLayout& lay = plan.packed_lay;
     heom::PackedRun pack{};
-    const int64_t elements = (int64_t)(h->t.n_ado - 1) * N * N;
-    const bool packed = n_steps > 0 && tiles > 0 && elements >= packed_min(h->d.precision, N) &&
-                        heom::packed_plan(j, h->d.precision, h->info.sigma0_bytes, need - records_bytes,
-                                          heom::control_bytes(N), &lay);
-    // small matrices: one column per lane, in tiles inside the run
-    const bool columns = n_steps > 0 && tiles > 0 && heom::columns_eligible(j, h->d.precision) &&
-                         (h->t.n_ado - 2) / (64 / N) + 1 >= columns_min(h->d.precision);
     void* z = nullptr;
     if (packed) {
         for (int k = 0; k < 3; ++k) {
@@ -1166,30 +1190,52 @@ heom_status heom_propagate(const heom_hierarchy* h, heom_state io, void* work_de
 // (100 MHz ticks; 0 = the first unanswered poll gives up, < 0 = the default).
 void heom_test_resident_wait(int64_t ticks) { t_resident_wait_ticks = ticks; }
 
-// Not part of the ABI, host only: how a run of `problem` is done: 0 = stage by
-// stage, 1 = one workgroup, 2 = a grid; out = end of what its launches use of the
+static bool host_job(const heom_problem* problem, int32_t hermitian, heom_hierarchy* h, heom::Job* j) {
+    if (derive(problem, h->d) != HEOM_OK) return false;
+    fill_info(h->d, &h->info);
+    h->t.N = h->d.N;
+    h->t.W = h->d.W;
+    h->t.D = h->d.D;
+    h->t.n_ado = (int32_t)h->d.n_ado;
+    h->t.h_complex = h->d.h_complex ? 1 : 0;
+    *j = base_job(h);
+    j->herm = hermitian ? 1 : 0;
+    return true;
+}
+
+// Not part of the ABI, host only: whether a run of `problem` is a resident one:
+// 0 = no, 1 = one workgroup, 2 = a grid; out = end of what its launches use of the
 // workspace in front of the records, the size of that, LDS bytes per workgroup,
 // workgroups.
 int32_t heom_test_resident_plan(const heom_problem* problem, int32_t hermitian, size_t out[4]) {
     heom_hierarchy h{};
-    if (derive(problem, h.d) != HEOM_OK) return -1;
-    fill_info(h.d, &h.info);
-    h.t.N = h.d.N;
-    h.t.W = h.d.W;
-    h.t.D = h.d.D;
-    h.t.n_ado = (int32_t)h.d.n_ado;
-    h.t.h_complex = h.d.h_complex ? 1 : 0;
-    heom::Job j = base_job(&h);
-    j.herm = hermitian ? 1 : 0;
-    heom::ResidentPlan plan;
-    heom::ResidentLayout lay;
-    if (!resident_takes(j, h.d.precision, h.info, h.info.work_bytes, &plan, &lay)) return 0;
-    out[0] = lay.end;
+    heom::Job j;
+    if (!host_job(problem, hermitian, &h, &j)) return -1;
+    const RunPlan p = run_plan(j, h.d.precision, h.info, h.info.work_bytes, true);
+    if (p.form != RunForm::kResident) return 0;
+    out[0] = p.resident_lay.end;
     out[1] = h.info.work_bytes;
-    out[2] = plan.lds;
-    out[3] = (size_t)plan.groups + (plan.grid ? 1 : 0);
-    return plan.grid ? 2 : 1;
+    out[2] = p.resident.lds;
+    out[3] = (size_t)p.resident.groups + (p.resident.grid ? 1 : 0);
+    return p.resident.grid ? 2 : 1;
 }
+
+// Not part of the ABI, host only: the kernel of the ADOs u >= 1 in a run of
+// `problem` on this thread (NULL: not a valid problem).
+const char* heom_test_run_kernel(const heom_problem* problem, int32_t hermitian) {
+    heom_hierarchy h{};
+    heom::Job j;
+    if (!host_job(problem, hermitian, &h, &j)) return nullptr;
+    switch (run_plan(j, h.d.precision, h.info, h.info.work_bytes, true).form) {
+        case RunForm::kResident: return "k_resident";
+        case RunForm::kPacked: return "k_packed";
+        case RunForm::kColumns: return "k_columns";
+        default: return heom::stage_kernel_name(j, h.d.precision);
+    }
+}
+
+// Not part of the ABI: runs of this thread are not resident ones.
+void heom_test_resident_off(int32_t off) { t_resident_off = off != 0; }
 
 // Not part of the ABI: runs of this thread are packed from so many elements
 // on (< 0 = the library's choice).

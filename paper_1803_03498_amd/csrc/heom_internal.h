@@ -297,6 +297,8 @@ int bulk_ados_per_tile(int N, int W, int D, int tsize);
 // Device address and size of this device's static scratch array (looked up
 // once per device, with that device current; thread-safe).
 hipError_t scratch_buffer(void** out, size_t* bytes);
+// The kernel that launch_stage takes for the ADOs u >= 1 of a single job.
+const char* stage_kernel_name(const Job& j, int precision);
 // Name of the kernel whose launch failed in the last launch_stage call on this thread.
 const char* last_launch_failure();
 // Which bulk kernel a job uses: 0 = FMA path, otherwise 16*nb >= N on the MFMA path.
@@ -324,7 +326,7 @@ heom_status problem_rate_bound(const heom_problem* p, double* rate);
 bool block_step_ok(const heom_problem* p, double dt);
 double rk4_real_limit();
 void set_last_error(const std::string& msg);
-void rk4_stage_specs(StageSpec sp[4]);
-void rk4_twelve(Job* j, int precision, StageSpec sp[4]);           // the four classic RK4 stages
+void rk4_stage_specs(StageSpec sp[4]);           // the four classic RK4 stages
+void rk4_twelve(Job* j, int precision, StageSpec sp[4]);
 double monotonic_seconds();
 }  // namespace heom

@@ -1927,6 +1927,24 @@ static hipError_t launch_small_h(const Job& single, const StageSpec& sp, hipStre
 
 thread_local const char* g_launch_what = "";
 
+// The kernel of a launch's ADOs u >= 1.
+enum class StageKernel { kPersist, kMfma, kSmall, kFma };
+static StageKernel stage_kernel(const Job& single, bool batched, int tsize) {
+    if (tsize == 4 && persist_blocks(single, batched) > 0) return StageKernel::kPersist;
+    if (bulk_mfma_blocks(single.t.N, single.t.h_complex != 0, tsize == 8 ? 0 : 1) > 0) return StageKernel::kMfma;
+    return !batched && small_eligible(single, tsize) ? StageKernel::kSmall : StageKernel::kFma;
+}
+
+const char* stage_kernel_name(const Job& j, int precision) {
+    if (precision == 2) return "k_bulk_mfma_pk";
+    switch (stage_kernel(j, false, precision == 0 ? 8 : 4)) {
+        case StageKernel::kPersist: return "k_stage_persist";
+        case StageKernel::kMfma: return "k_bulk_mfma";
+        case StageKernel::kSmall: return "k_stage_small";
+        default: return "k_bulk_fma";
+    }
+}
+
 template <typename T>
 static hipError_t launch_stage_t(const Job& single, const Job* jobs_dev, int n_jobs,
                                  int total_tiles, const StageSpec& sp, hipStream_t stream,
@@ -1946,13 +1964,13 @@ static hipError_t launch_stage_t(const Job& single, const Job* jobs_dev, int n_j
     // MFMA path for 16 <= N (real H); FP64 above N = 48 would need more than
     // 160 KiB of LDS and stays on the FMA path.  sigma_0 rides along with the
     // bulk launch where its LDS fits.
-    const int pb = sizeof(T) == 4 ? persist_blocks(single, batched) : 0;
-    if (pb > 0) {
+    const StageKernel kernel = stage_kernel(single, batched, (int)sizeof(T));
+    if (kernel == StageKernel::kPersist) {
         // one tile per ADO u >= 1 (the job's tile count may group small ADOs
         // for the FMA kernel)
         const int n_ados = single.t.n_ado - 1;
         if (ev_begin && (e = hipEventRecord(ev_begin, stream)) != hipSuccess) return e;
-        switch (pb) {
+        switch (persist_blocks(single, batched)) {
             case 1: e = launch_persist_nb<1>(single, n_ados, sp, stream); break;
             case 2: e = launch_persist_nb<2>(single, n_ados, sp, stream); break;
             case 3: e = launch_persist_nb<3>(single, n_ados, sp, stream); break;
@@ -1965,12 +1983,12 @@ static hipError_t launch_stage_t(const Job& single, const Job* jobs_dev, int n_j
         if (ev_end) e = hipEventRecord(ev_end, stream);
         return e;
     }
-    const int nb = bulk_mfma_blocks(N, single.t.h_complex != 0, sizeof(T) == 8 ? 0 : 1);
-    if (nb > 0) {
+    if (kernel == StageKernel::kMfma) {
+        const int nb = bulk_mfma_blocks(N, single.t.h_complex != 0, sizeof(T) == 8 ? 0 : 1);
         if (ev_begin && (e = hipEventRecord(ev_begin, stream)) != hipSuccess) return e;
         e = launch_mfma<T>(nb, single.herm != 0, single, jobs_dev, n_jobs, total_tiles, sp, stream, n_s0);
         if (e != hipSuccess) g_launch_what = "MFMA bulk stage kernel";
-    } else if (!batched && small_eligible(single, (int)sizeof(T))) {
+    } else if (kernel == StageKernel::kSmall) {
         if (ev_begin && (e = hipEventRecord(ev_begin, stream)) != hipSuccess) return e;
         e = single.herm ? launch_small_h<T, true>(single, sp, stream)
                         : launch_small_h<T, false>(single, sp, stream);
