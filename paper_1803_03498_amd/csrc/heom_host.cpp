@@ -942,12 +942,32 @@ heom_status resident_run(const heom_hierarchy* h, const heom::Job& j, const heom
 // / 155, 36 states, 703 ADOs 163 / 192; packed storage, 23 states, 2600 ADOs 104
 // / 108, 24 states, 2925 ADOs 120 / 109).  FP64 below 16 states would take the
 // FMA kernels instead (14 states, 3060 ADOs 139 / 77; 16 states, 4845 ADOs, on
-// the matrix cores either way, 94 / 99).
+// the matrix cores either way, 94 / 99).  Packed storage with three row blocks
+// gains later: 44 states, 946 ADOs 179 / 206, 1035 ADOs 176 / 194, 48 states, 969
+// ADOs 203 / 206, 2925 ADOs 292 / 238.
+//
+// The "+" sums are the work of the ADOs below the top level.  In FP32, where the
+// unpacked kernel is at its best (two row blocks, element pairs), they outweigh
+// the bytes of deep hierarchies, with more than 0.3 of the ADOs below the top:
+// 22 states of 11 modes at depth 7 460 / 486, 26 of 8 at depth 8 260 / 305, of 13
+// at depth 6 490 / 496, 28 of 9 at depth 7 251 / 277, 30 of 10 at depth 8 993 /
+// 1071 (one mode per coupled state; at best 24 of 12 at depth 6 321 / 303).  Several
+// modes per state share their rows' places, and odd N has slower single elements:
+// there packing pays from about 10 million elements (22 states of 10 modes, 9.4
+// million 304 / 311, 24 of 10, 11.2 million 375 / 325; 27 of 9, 8.3 million 253 /
+// 268, 25 of 12, 11.6 million 387 / 346).
 thread_local int64_t t_packed_min = -1;  // this thread's bound instead, for tests
-int64_t packed_min(int precision, int N) {
+int64_t packed_min(const Derived& d) {
     if (t_packed_min >= 0) return t_packed_min;
-    if (precision == HEOM_FP64) return N < 16 ? 600000 : 1600000;
-    return precision == HEOM_FP32_HERM ? 1500000 : 7000000;
+    const int N = d.N;
+    if (d.precision == HEOM_FP64) return N < 16 ? 600000 : 1600000;
+    if (d.precision == HEOM_FP32_HERM) return N > 32 && N <= 48 ? 2100000 : 1500000;
+    if (N >= 18 && N < 32 && 10 * d.n_low > 3 * d.n_ado) {
+        int coupled = 0;
+        for (int s = 0; s < N; ++s) coupled += d.state_mode_begin[s + 1] > d.state_mode_begin[s];
+        return N >= 20 && N % 2 == 0 && coupled == d.W ? INT64_MAX : 10000000;
+    }
+    return 7000000;
 }
 
 // Tiles (of 64 / N ADOs, one per wavefront) from which a hierarchy of 2 to 8
@@ -971,13 +991,13 @@ struct RunPlan {
 };
 
 // stage_bytes: the workspace in front of the records.
-RunPlan run_plan(const heom::Job& j, int precision, const heom_info& info, size_t stage_bytes, bool resident) {
+RunPlan run_plan(const heom::Job& j, const Derived& d, const heom_info& info, size_t stage_bytes, bool resident) {
     RunPlan p;
-    const int N = j.t.N;
+    const int N = d.N, precision = d.precision;
     if (j.t.n_ado < 2) return p;
     if (resident && resident_takes(j, precision, info, stage_bytes, &p.resident, &p.resident_lay)) {
         p.form = RunForm::kResident;
-    } else if ((int64_t)(j.t.n_ado - 1) * N * N >= packed_min(precision, N) &&
+    } else if ((int64_t)(j.t.n_ado - 1) * N * N >= packed_min(d) &&
                heom::packed_plan(j, precision, info.sigma0_bytes, stage_bytes, heom::control_bytes(N),
                                  &p.packed_lay)) {
         // large Hermitian runs keep their ADOs packed between the first and the
@@ -1036,14 +1056,14 @@ heom_status propagate_impl(const heom_hierarchy* h, heom_state io, void* work_de
     int64_t done = 0;
     int32_t status = 0;
     RunPlan plan;
-    if (n_steps > 0) plan = run_plan(j, h->d.precision, h->info, need - records_bytes, true);
+    if (n_steps > 0) plan = run_plan(j, h->d, h->info, need - records_bytes, true);
     if (plan.form == RunForm::kResident) {
         s = resident_run(h, j, plan.resident, plan.resident_lay, w, ctl, n_steps, timed, host_out, n_rec * rd, st,
                          &done, &status);
         if (s != HEOM_OK || done == n_steps) return s;
         // given up (the GPU could not hold the launch): the stage kernels go
         // on from the last committed step
-        plan = run_plan(j, h->d.precision, h->info, need - records_bytes, false);
+        plan = run_plan(j, h->d, h->info, need - records_bytes, false);
     }
     std::memcpy(ctl, &done, 8);
     std::memcpy(ctl + 256, &status, 4);
@@ -1211,7 +1231,7 @@ int32_t heom_test_resident_plan(const heom_problem* problem, int32_t hermitian, 
     heom_hierarchy h{};
     heom::Job j;
     if (!host_job(problem, hermitian, &h, &j)) return -1;
-    const RunPlan p = run_plan(j, h.d.precision, h.info, h.info.work_bytes, true);
+    const RunPlan p = run_plan(j, h.d, h.info, h.info.work_bytes, true);
     if (p.form != RunForm::kResident) return 0;
     out[0] = p.resident_lay.end;
     out[1] = h.info.work_bytes;
@@ -1226,7 +1246,7 @@ const char* heom_test_run_kernel(const heom_problem* problem, int32_t hermitian)
     heom_hierarchy h{};
     heom::Job j;
     if (!host_job(problem, hermitian, &h, &j)) return nullptr;
-    switch (run_plan(j, h.d.precision, h.info, h.info.work_bytes, true).form) {
+    switch (run_plan(j, h.d, h.info, h.info.work_bytes, true).form) {
         case RunForm::kResident: return "k_resident";
         case RunForm::kPacked: return "k_packed";
         case RunForm::kColumns: return "k_columns";
