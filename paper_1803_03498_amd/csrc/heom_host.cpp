@@ -837,9 +837,14 @@ private:
 ResidentPermit::Slot ResidentPermit::slots_[64];
 
 // Steps per resident launch (bounds the time one launch holds its compute
-// units: about 50 ms at 3060 ADOs), and the bound of each of its waits (0.2 s).
+// units: about 50 ms at 3060 ADOs), and the bound of each of its waits (5 ms).
+// The wait is for compute units that other streams' kernels hold (a run of 3060
+// ADOs next to one of 156849 ADOs of 48 x 48 or 12.3 million of 7 x 7: no launch
+// gave up at 5 ms, some at 2), and it is lost where launches of other processes
+// wait for each other: four processes with 30 runs of 3060 ADOs each took 1.9 s
+// with a bound of 0.2 s, 0.12 s with 5 ms, 0.18 s by the stage kernels.
 constexpr int64_t kResidentSteps = 4096;
-constexpr uint64_t kResidentWaitTicks = 20000000ull;
+constexpr uint64_t kResidentWaitTicks = 500000ull;
 // this thread's bound instead, for tests of a launch that gives up
 thread_local int64_t t_resident_wait_ticks = -1;
 thread_local bool t_resident_off = false;  // this thread's runs take the other forms, for tests
