@@ -174,27 +174,12 @@ def _cpu_model():
     return platform.processor() or platform.machine()
 
 
-def _bulk_kernel_name(info, precision, N, heom):
-    """The stage kernel that propagates ADOs u >= 1 of a Hermitian run with a
-    real H (the library's rules, whose reasons stand beside them in
-    heom_host.cpp, heom_packed.hip and heom_resident.hip)."""
-    n = info["n_ado"]
-    elements = (n - 1) * N * N
-    fp64 = precision == heom.FP64
-    if precision != heom.FP32_HERM and N <= 22 and elements <= 256 * 2048:
-        return "k_resident"
-    if (10 if fp64 else 17) <= N <= (48 if fp64 else 64) and elements >= (
-            (600000 if N < 16 else 1600000) if fp64 else 1500000 if precision == heom.FP32_HERM else 7000000):
-        return "k_packed"
-    if precision != heom.FP32_HERM and 2 <= N <= 8 and (n - 2) // (64 // N) + 1 >= (2048 if fp64 else 2400):
-        return "k_columns"
-    if precision == heom.FP32_MIXED and 10 <= N <= 64:
-        return "k_stage_persist"
-    if not info["bulk_kernel"]:
-        # single propagations with N <= 16 and >= 32768 ADOs take the
-        # persistent FMA kernel
-        return "k_stage_small" if N <= 16 and info["n_ado"] >= 32768 else "k_bulk_fma"
-    return "k_bulk_mfma_pk" if precision == heom.FP32_HERM else "k_bulk_mfma"
+def _bulk_kernel_name(prob, precision, heom):
+    """The kernel that propagates ADOs u >= 1 of a Hermitian run, as the
+    library decides."""
+    fn = heom.load().heom_test_run_kernel
+    fn.argtypes, fn.restype = [ctypes.c_void_p, ctypes.c_int32], ctypes.c_char_p
+    return fn(ctypes.byref(heom.Problem(prob, precision).struct), 1).decode()
 
 
 def _table_bytes_per_launch(kernel, n, W, D, fp64):
@@ -238,11 +223,12 @@ def _fp64_reference(heom, torch, lib, prob, precision, steps, rec_every, N, n):
             kbytes = ctypes.c_double()
             lib.heom_timing_read(ctypes.byref(ms), ctypes.byref(launches), ctypes.byref(kbytes), 1)
             avg = ms.value / 1e3 / max(launches.value, 1)
-            achieved = kbytes.value / max(launches.value, 1) / avg / 1e9
+            kernel = _bulk_kernel_name(prob, prec, heom)
+            achieved = None if kernel == "k_resident" else kbytes.value / max(launches.value, 1) / avg / 1e9
             out.update({"ms_per_step": 1e3 * el / steps, "ado_updates_per_s": n * steps / el,
-                        "bulk_kernel": _bulk_kernel_name(h.info, prec, N, heom),
+                        "bulk_kernel": kernel,
                         "avg_launch_ms": avg * 1e3, "achieved_GBps": achieved,
-                        "frac": achieved / HBM_PEAK_GBS, "steps": steps,
+                        "frac": achieved and achieved / HBM_PEAK_GBS, "steps": steps,
                         "note": "complex128 throughout, same workload, untimed in the line's value"})
         del st, work, h
         torch.cuda.empty_cache()
@@ -754,13 +740,15 @@ def main():
     kbytes = ctypes.c_double()
     lib.heom_timing_read(ctypes.byref(ms), ctypes.byref(launches), ctypes.byref(kbytes), 1)
 
-    kernel_short = _bulk_kernel_name(info, precision, N, heom)
-    kernel_name = kernel_short + " (RK4 stage, ADOs u>=1)"
+    kernel_short = _bulk_kernel_name(prob, precision, heom)
+    resident = kernel_short == "k_resident"  # keeps its ADOs on the compute units
+    kernel_name = kernel_short + (" (whole run)" if resident else " (RK4 stage, ADOs u>=1)")
     traffic = measured_traffic(kernel_short, args.workload, args.precision)
     elapsed = t1 - t0
     ms_per_step = 1e3 * elapsed / steps
     ado_updates = n * steps / elapsed
-    # what the stages of this run move, neighbour rows counted once
+    # what the stages of this run move, neighbour rows counted once (a run in one
+    # launch has no such rate)
     step_bytes = kbytes.value / steps + 13.0 * N * N * 16
     hbm_gbs = step_bytes * steps / elapsed / 1e9
     avg_launch_s = ms.value / 1e3 / max(launches.value, 1)
@@ -811,7 +799,7 @@ def main():
         "vs_baseline": None,
         "dtype": "f64" if precision == heom.FP64 else "f32",
         "data": "synthetic",
-        "hbm_GBps_algorithmic": hbm_gbs,
+        "hbm_GBps_algorithmic": None if resident else hbm_gbs,
         "config": {
             "workload": "%s: %d sites, W=%d modes, depth %d, %d ADOs of %dx%d %s; RK4 dt=%g fs"
                         % (args.workload, N, W_modes, prob["depth"], n, N, N,
@@ -820,22 +808,22 @@ def main():
                             heom.FP64: "complex128"}[precision], prob["dt_fs"]),
             "n_ado": n, "n_states": N, "n_modes": W_modes, "depth": prob["depth"],
             "precision": args.precision, "record_every": rec_every,
-            "bytes_per_step_algorithmic": step_bytes,
+            "bytes_per_step_algorithmic": None if resident else step_bytes,
         },
         "roofline": {
             "kernel": kernel_name,
-            "bound": "hbm",
-            "achieved": achieved,
+            "bound": "latency" if resident else "hbm",
+            "achieved": None if resident else achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS,
+            "frac": None if resident else achieved / HBM_PEAK_GBS,
             "traffic": traffic,
             "avg_launch_ms": avg_launch_s * 1e3,
-            "bytes_per_launch_algorithmic": bytes_per_launch,
+            "bytes_per_launch_algorithmic": None if resident else bytes_per_launch,
             "table_bytes_per_launch": _table_bytes_per_launch(
                 kernel_short, n, W_modes, prob["depth"], precision == heom.FP64),
             "device_copy_GBps": copy_gbs,
-            "frac_of_device_copy": achieved / copy_gbs,
+            "frac_of_device_copy": None if resident else achieved / copy_gbs,
         },
         "cpu_baseline": cpu,
         "fp64": fp64,

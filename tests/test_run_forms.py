@@ -42,3 +42,14 @@ def _prob(N, nb, M, D):
 ])
 def test_packed_where_it_pays(precision, N, nb, M, D, kernel):
     assert rf.run_kernel(_prob(N, nb, M, D), precision) == kernel
+
+
+def test_bench_names_the_kernel_that_runs():
+    """Sizes that one launch could hold by their elements, and does not by its
+    LDS (16 states, 1820 ADOs) or for its workspace (495 ADOs of 2 x 2 in FP32)."""
+    import bench
+    import paper_1803_03498_amd as heom
+    assert bench._bulk_kernel_name(_prob(16, 12, 0, 4), FP64, heom) == "k_bulk_mfma"
+    assert bench._bulk_kernel_name(_prob(16, 12, 0, 4), FP32, heom) == "k_resident"
+    assert bench._bulk_kernel_name(_prob(2, 2, 1, 8), FP32, heom) == "k_bulk_fma"
+    assert bench._bulk_kernel_name(_prob(24, 3, 2, 10), FP64, heom) == "k_bulk_mfma"  # depth above the modes
