@@ -219,9 +219,12 @@ heom_status heom_rhs(const heom_hierarchy* h, heom_state in, heom_state out, int
  * HEOM_E_NUMERIC if a recorded observable was not finite.  Small hierarchies
  * (HEOM_FP64, Hermitian HEOM_FP32_MIXED; N <= 22, up to about 255 workgroups of
  * 2048 elements) run all their steps in one launch that keeps the state on the
- * compute units.  Large Hermitian runs (real H) keep their ADOs packed, or for
- * N <= 8 in another order, inside the call: io.rest holds the state again when
- * it returns HEOM_OK or HEOM_E_NUMERIC.  Stage by stage, runs of 8 steps or
+ * compute units, where its flags and stage copies fit the planned workspace (all
+ * but a few sizes of FP32 with N <= 2).  Large Hermitian runs (real H) keep their
+ * ADOs packed (HEOM_FP64 and HEOM_FP32_MIXED only up to a depth of the number of
+ * modes: beyond it the planned workspace does not hold the packed arrays), or for
+ * N <= 8 in another order, inside the call: io.rest holds the state again when it
+ * returns HEOM_OK or HEOM_E_NUMERIC.  Stage by stage, runs of 8 steps or
  * more launch the first step directly and replay a HIP graph of one step
  * (captured on a private stream) for the rest, unless kernel timing is on
  * (heom_timing_enable); the results are the same either way, bit for bit. */

@@ -176,6 +176,10 @@ struct PackedRun {
     void* h;                      // H in operand order, or null
     void* complex_rest;           // the caller's complex ADOs, null if packed
 };
+// false also where the packed arrays do not fit: a complex state's workspace holds
+// y, two stages and Z (half an array each) and the mirrors of half the ADOs at
+// most, which is all of those below the top level while the depth is at most the
+// number of modes.
 bool packed_plan(const Job& j, int precision, size_t sigma0_bytes, size_t work_bytes, size_t offset,
                  PackedLayout* layout);
 // Packs the state (Job::rest[0] from complex_rest), runs stage k of a step
