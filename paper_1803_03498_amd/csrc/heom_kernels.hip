@@ -1696,7 +1696,15 @@ static hipError_t launch_persist_t(const Job& single, int total_tiles, const Sta
     // two workers per CU for N > 32 (measured faster than the three that the
     // registers of the stage without bases allow); up to sixteen 2-wave
     // workers for N <= 16
-    const int cap = NB >= 3 ? 2 : 16;
+    int cap = NB >= 3 ? 2 : 16;
+    // With bases above 48 states a worker of its own per CU, and sigma_0 riding
+    // along in the LDS that this leaves: with two, sigma_0 above 50 states has no
+    // room and takes a launch of its own (64 states, 1653 ADOs 562 us per step
+    // against 408; 54 states, 55 ADOs 318 against 258).  50 states and more than
+    // four rounds of ADOs: two (1287 ADOs 235 against 268, 925 ADOs 213 against 205).
+    if (NB == 4 && NBASE > 0 &&
+        (total_tiles <= 1024 || sigma0_lds(single.t.N, single.t.W, 4, false, 0).total > 80 * 1024))
+        cap = 1;
     int by_regs = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&by_regs, fn, NT, own) != hipSuccess || by_regs < 1)
         by_regs = 1;
