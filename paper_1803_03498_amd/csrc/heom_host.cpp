@@ -1375,17 +1375,18 @@ heom_status heom_propagate_block(const heom_hierarchy* h, void* state, void* wor
     double* rec = reinterpret_cast<double*>(w + 256 + 3 * copy);
     const int64_t n_rec = heom_record_count(n_steps, record_every);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // status at 0, steps done at 8, commit word at 16
-    HIP_TRY(hipMemsetAsync(status, 0, 24, st));
+    // status at 0, steps done at 8, commit word at 16 (32 bytes: one launch)
+    HIP_TRY(hipMemsetAsync(status, 0, 32, st));
     hipError_t e = hipSuccess;
     int64_t done = 0;
     heom::ResidentPlan plan;
     // A grid's launch builds its link lists first, which a step or two do not
     // pay for (us per call, stage by stage / one launch: one step of 7 states,
-    // 3060 ADOs 100 / 112, 24 states, 325 ADOs 107 / 111, 40 states, 861 ADOs 125
-    // / 119; four elements per thread, 10 states, 10626 ADOs: one step 116 / 142,
-    // two 165 / 173, three 215 / 205).  Either way gives the same bits.
-    auto pays = [&] { return !plan.grid || n_steps >= (plan.ept == 4 ? 3 : N <= 32 ? 2 : 1); };
+    // 3060 ADOs 100 / 112, 25 states, 76 ADOs 100 / 108, 40 states, 861 ADOs 125 /
+    // 119; four elements per thread: 10 states, 10626 ADOs one step 116 / 142, two
+    // 165 / 173, three 215 / 205, 56 states, 1653 ADOs one step 166 / 158, two 268 /
+    // 207).  Either way gives the same bits.
+    auto pays = [&] { return !plan.grid || n_steps >= (N > 32 ? 1 : plan.ept == 4 && N <= 16 ? 3 : 2); };
     if (n_steps > 0 && heom::resident_block_plan(h->t, (int)h->d.n_low, &plan) && pays() &&
         (!plan.grid || copy >= kResidentFlagBytes)) {
         heom::ResidentArgs a{};
