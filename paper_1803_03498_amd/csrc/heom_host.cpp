@@ -980,10 +980,22 @@ int64_t packed_min(const Derived& d) {
 // waits are not covered (us per step, one thread per element / one column per
 // lane: FP32 1856 tiles 89 / 118, 2544 tiles 126 / 115, 4307 tiles 170 / 155,
 // 6359 tiles 250 / 109; FP64 1609 tiles 152 / 164, 2544 tiles 191 / 139).
+// Below the top level a wavefront loads the "+" rows of a tile in B batches of up
+// to four modes of one state, one batch after the other, 3.5 us each per stage in
+// either precision.  Where the modes are many and the depth is small, there are too
+// few tiles to share that, and the tiles of the whole have to outweigh it (FP32: 7
+// states, 18 batches, 5085 tiles 177 / 249; 5 states, 30, 17013 tiles 308 / 397; 6
+// states, 36, 34951 tiles 554 / 638, 12, 4638 tiles 147 / 170, but 5 states, 12, 6855
+// tiles 190 / 141, 40, 45942 tiles 1174 / 741; FP64: 4 states, 16, 2482 tiles 175 /
+// 239; 5 states, 30, 17013 tiles 447 / 537, but 2 states, 12, 5100 tiles 254 / 214; 6
+// states, 24, 14289 tiles 466 / 378; 7 states, 36, 47615 tiles 1584 / 1270).
 thread_local int64_t t_columns_min = -1;  // this thread's bound instead, for tests
-int64_t columns_min(int precision) {
+int64_t columns_min(const Derived& d) {
     if (t_columns_min >= 0) return t_columns_min;
-    return precision == HEOM_FP64 ? 2048 : 2400;
+    int64_t B = 0;
+    for (int s = 0; s < d.N; ++s) B += (d.state_mode_begin[s + 1] - d.state_mode_begin[s] + 3) / 4;
+    return d.precision == HEOM_FP64 ? std::max<int64_t>({2048, 320 * B, 42 * B * B - 530 * B})
+                                    : std::max<int64_t>(2400, 18 * B * B + 345 * B);
 }
 
 // How a run of at least one step is done.
@@ -1008,7 +1020,7 @@ RunPlan run_plan(const heom::Job& j, const Derived& d, const heom_info& info, si
         // large Hermitian runs keep their ADOs packed between the first and the
         // last step
         p.form = RunForm::kPacked;
-    } else if (heom::columns_eligible(j, precision) && (j.t.n_ado - 2) / (64 / N) + 1 >= columns_min(precision)) {
+    } else if (heom::columns_eligible(j, precision) && (j.t.n_ado - 2) / (64 / N) + 1 >= columns_min(d)) {
         // small matrices: one column per lane, in tiles inside the run
         p.form = RunForm::kColumns;
     }

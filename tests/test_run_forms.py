@@ -39,8 +39,21 @@ def _prob(N, nb, M, D):
     (HERM, 33, 33, 1, 3, "k_packed"),
     (FP64, 26, 8, 0, 7, "k_packed"),
     (FP64, 48, 48, 1, 3, "k_packed"),
+    # one column per lane: the tiles outweigh the "+" links below the top level
+    (FP32, 7, 3, 20, 3, "k_stage_small"),
+    (FP32, 5, 5, 20, 3, "k_stage_small"),
+    (FP32, 6, 6, 20, 3, "k_stage_small"),
+    (FP32, 6, 6, 4, 4, "k_stage_small"),
+    (FP32, 5, 5, 2, 8, "k_columns"),
+    (FP32, 7, 7, 5, 6, "k_columns"),
+    (FP32, 5, 5, 30, 3, "k_columns"),
+    (FP64, 4, 4, 14, 3, "k_stage_small"),
+    (FP64, 5, 5, 20, 3, "k_stage_small"),
+    (FP64, 2, 2, 20, 4, "k_columns"),
+    (FP64, 6, 3, 30, 3, "k_columns"),
+    (FP64, 7, 7, 5, 6, "k_columns"),
 ])
-def test_packed_where_it_pays(precision, N, nb, M, D, kernel):
+def test_kernel_where_it_pays(precision, N, nb, M, D, kernel):
     assert rf.run_kernel(_prob(N, nb, M, D), precision) == kernel
 
 
