@@ -220,7 +220,9 @@ heom_status heom_rhs(const heom_hierarchy* h, heom_state in, heom_state out, int
  * (HEOM_FP64, Hermitian HEOM_FP32_MIXED; N <= 22, up to about 255 workgroups of
  * 2048 elements) run all their steps in one launch that keeps the state on the
  * compute units, where its flags and stage copies fit the planned workspace (all
- * but a few sizes of FP32 with N <= 2).  Large Hermitian runs (real H) keep their
+ * but a few sizes of FP32 with N <= 2); if other work on the GPU leaves such a
+ * launch no room within 5 ms, the stage kernels go on from its last committed
+ * step, and the last bits of the result are theirs.  Large Hermitian runs (real H) keep their
  * ADOs packed (HEOM_FP64 and HEOM_FP32_MIXED only up to a depth of the number of
  * modes: beyond it the planned workspace does not hold the packed arrays), or for
  * N <= 8 in another order, inside the call: io.rest holds the state again when it
